@@ -94,6 +94,14 @@ __device__ inline double dpp(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// A row's last lane broadcast to the next row (kDppBcast15), the second row's to
+// the third and fourth (kDppBcast31); rows outside ROWS get +0.
+enum { kDppBcast15 = 0x142, kDppBcast31 = 0x143 };
+template <int CTRL, int ROWS>
+__device__ inline float dpp_rows(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
+}
+
 // Sum over aligned groups of 2, 4, 8 or 16 lanes; every lane of a group
 // ends with the same bits (each step adds two values that the partner adds
 // in the other order).

@@ -195,13 +195,15 @@ __host__ __device__ inline int body_floats() { return 32 * kMaxBodies; }
 __host__ __device__ inline int joint_floats() { return 16 * kMaxJoints; }  // tau, Jc[12], a, b, type|flags
 __host__ __device__ inline int contact_floats() { return 12 * kMaxContacts; }  // point, normal, gap, mu, a, b, key, slot
 __host__ __device__ inline int row_floats(int mc) { return 18 * mc; }
-__host__ __device__ inline int vec_floats(int mc) { return 15 * mc; }
+__host__ __device__ inline int vec_floats(int mc) { return 14 * mc; }
 __host__ __device__ inline int bodyw_floats() { return 2 * 6 * kMaxBodies; }  // FP64 [6][kMaxBodies]
 __host__ __device__ inline int posed_floats() { return 2 * 7 * kMaxBodies; }  // FP64 poses [7][kMaxBodies]
-__host__ __device__ inline int inc_floats(int mc) { return ((kMaxBodies + 1 + 2 * mc) + 3) & ~3; }
+__host__ __device__ inline int inc_floats(int mc) { return ((kMaxBodies + 1 + 2 * mc + 12) + 3) & ~3; }  // and twelve hand-over ints
+// t of the x update: the rows, and zeros up to the last row a thread's slots reach
+__host__ __device__ inline int t_floats(int mc) { return mc + mc / 2 + 64 + 64; }
 __host__ __device__ inline int smem_floats(int mc) {
     return body_floats() + joint_floats() + contact_floats() + row_floats(mc) + vec_floats(mc) +
-           tri_row_offset(mc) + 64 + bodyw_floats() + posed_floats() + inc_floats(mc);
+           tri_row_offset(mc) + 64 + bodyw_floats() + posed_floats() + inc_floats(mc) + t_floats(mc);
 }
 
 }  // namespace kamx

@@ -39,7 +39,7 @@ enum { CP = 0, CN = 3, CGAP = 6, CMU = 7, CA = 8, CB = 9, CKEY = 10 };
 // row fields [field][MC]
 enum { RJ = 0, RBIAS = 12, RMU = 13, RIA = 14, RIB = 15, RKIND = 16, RREG = 17 };
 // vector fields [field][MC]
-enum { VP = 0, VRHO, VVT, VX, VYH, VZH, VYP, VZP, VRHS, VT, VXN, VWS, VAUX, VCOL, VDX };
+enum { VP = 0, VRHO, VVT, VX, VYH, VZH, VYP, VZP, VRHS, VXN, VWS, VAUX, VCOL, VDX };
 
 struct Lds {
     float *b, *j, *c, *r, *v, *A, *red;
@@ -47,6 +47,8 @@ struct Lds {
     double *qd;          // [7][kMaxBodies] FP64 poses the rows are built at
     int *inc_off;        // [kMaxBodies + 1] body -> row incidence offsets
     int *inc_list;       // [2 * MC] (row << 1) | side
+    float *t;            // [t_floats(MC)] t = X r of the x update, 0 past the world's rows
+    int *s_int;          // [12] values one thread hands to all
     int mc;
     __device__ float &bf(int f, int i) const { return b[f * kMaxBodies + i]; }
     __device__ float &jfld(int f, int i) const { return j[f * kMaxJoints + i]; }
@@ -55,6 +57,49 @@ struct Lds {
     __device__ int &ri(int f, int i) const { return reinterpret_cast<int *>(r)[f * mc + i]; }
     __device__ float *vec(int f) const { return v + f * mc; }
 };
+
+// The workgroup's views of its dynamic LDS.
+template <int MC>
+__device__ inline Lds lds_views() {
+    extern __shared__ float4 smem4[];
+    float *sm = reinterpret_cast<float *>(smem4);
+    Lds L;
+    L.mc = MC;
+    L.b = sm;
+    L.j = L.b + body_floats();
+    L.c = L.j + joint_floats();
+    L.r = L.c + contact_floats();
+    L.v = L.r + row_floats(MC);
+    L.A = L.v + vec_floats(MC);
+    L.red = L.A + tri_row_offset(MC);
+    L.wb = reinterpret_cast<double *>(L.red + 64);
+    L.qd = L.wb + 6 * kMaxBodies;
+    L.inc_off = reinterpret_cast<int *>(L.red + 64 + bodyw_floats() + posed_floats());
+    L.inc_list = L.inc_off + kMaxBodies + 1;
+    L.s_int = L.inc_list + 2 * MC;
+    L.t = L.red + 64 + bodyw_floats() + posed_floats() + inc_floats(MC);
+    return L;
+}
+
+// The launch arguments where the kernel received them: read by scalar loads,
+// they and what follows from them (sizes, branches) are uniform to the compiler
+// and stay out of the vector registers.
+typedef const __attribute__((address_space(4))) StepArgs KernelArgs;
+typedef const __attribute__((address_space(4))) SolverParams SolverArgs;
+
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// a + b rounded by itself (never fused with a product that forms a or b)
+__device__ inline float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
+__device__ inline float uniform(float v) { return __int_as_float(uniform(__float_as_int(v))); }
+
+__device__ inline KernelArgs *uniform_args(KernelArgs *a) {
+    const uint64_t v = (uint64_t)a;
+    return (KernelArgs *)(((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v));
+}
 
 // world-frame rotation of a body (from LDS)
 __device__ inline void body_rot(const Lds &L, int b, float R[9]) {
@@ -93,7 +138,7 @@ __device__ inline void joint_geo(const Lds &L, const float *jf, int la, int lb, 
 }
 
 __device__ inline void put_row(const Lds &L, int r, const float Ja[6], int la, const float Jb[6], int lb, float f,
-                               int kind, float mu, const SolverParams &P) {
+                               int kind, float mu, SolverArgs &P) {
     for (int k = 0; k < 6; ++k) {
         L.rf(RJ + k, r) = Ja[k];
         L.rf(RJ + 6 + k, r) = lb >= 0 ? Jb[k] : 0.f;
@@ -115,7 +160,7 @@ __device__ inline void put_row(const Lds &L, int r, const float Ja[6], int la, c
 // Rows of joint j (5 rows from r0), Sec. 3 bilateral constraints; geometry
 // and constraint values in FP64, rows stored in FP32.
 __device__ inline void put_row6(const Lds &L, int r, const double Ja[6], int la, const double Jb[6], int lb, double f,
-                                int kind, const SolverParams &P) {
+                                int kind, SolverArgs &P) {
     float fa[6], fb[6];
     for (int k = 0; k < 6; ++k) {
         fa[k] = (float)Ja[k];
@@ -125,7 +170,7 @@ __device__ inline void put_row6(const Lds &L, int r, const double Ja[6], int la,
 }
 
 __device__ inline void joint_rows(const Lds &L, int type, const JointGeo &g, int la, int lb, int r0,
-                                  const SolverParams &P) {
+                                  SolverArgs &P) {
     joint_constraints(type, g, [&](int e, const double Ja[6], const double Jb[6], double f) {
         put_row6(L, r0 + e, Ja, la, Jb, lb, f, kRowBilateral, P);
     });
@@ -177,6 +222,38 @@ __device__ inline void reduce4(float &m0, float &m1, float &m2, float &s3, float
         m2 = max_nonneg(m2, red[4 * k + 2]);
         s3 = s3 + red[4 * k + 3];
     }
+}
+
+// The largest m (values of +0 or above, or NaN) and the sum s over the
+// workgroup, in reduce4's order: within rows of 16 lanes, the wave's four rows by
+// row broadcasts (lane 63 ends with (row 3 + row 2) + (row 1 + row 0)), the waves
+// in order through LDS.  Uniform results.
+template <int NT>
+__device__ inline void reduce_max_sum(float &m, float &s, float *red) {
+    m = lane_group_max<16>(m);
+    s = lane_group_sum<16>(s);
+    m = max_nonneg(m, dpp_rows<kDppBcast15, 0xa>(m));
+    s += dpp_rows<kDppBcast15, 0xa>(s);
+    m = max_nonneg(m, dpp_rows<kDppBcast31, 0xc>(m));
+    s += dpp_rows<kDppBcast31, 0xc>(s);
+    constexpr int NW = NT / 64;
+    if ((threadIdx.x & 63) == 63) {
+        red[2 * (threadIdx.x >> 6)] = m;
+        red[2 * (threadIdx.x >> 6) + 1] = s;
+    }
+    __syncthreads();
+    float v[2 * NW];
+#pragma unroll
+    for (int k = 0; k < 2 * NW; ++k) v[k] = red[k];
+    m = v[0];
+    s = v[1];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) {
+        m = max_nonneg(m, v[2 * k]);
+        s += v[2 * k + 1];
+    }
+    m = uniform(m);
+    s = uniform(s);
 }
 
 __device__ inline float dot4(const float *a, const float *b) {
@@ -258,54 +335,79 @@ __device__ inline void delassus_gather(const Lds &L, int nb, const float *vp, co
 // order, those nh first. The 12 (nb + nh) tasks run in passes of NT (one
 // pass when they fit); a pass starts at a multiple of NT, so the lanes of a
 // body's component form an aligned group of 4 or 2 within one wave.
-template <int NT>
-__device__ inline void delassus_gather_bal(const Lds &L, int nb, int nh, const unsigned char *gorder,
-                                           const float *vp, const float *x) {
-    const int nheavy = 24 * nh, ntask = nheavy + 12 * (nb - nh);
-    // one task per thread; the first pass is straight-line code, the rest
-    // (only when the tasks outnumber the threads) loops
-    auto task = [&](const int t) {
-        const bool heavy = t < nheavy;
-        int j, c, h, S;
-        if (heavy) {
-            j = t / 24;
-            const int r = t - 24 * j;
-            c = r >> 2;
-            h = r & 3;
-            S = 4;
-        } else {
-            const int u = t - nheavy, q = u / 12, r = u - 12 * q;
-            j = nh + q;
-            c = r >> 1;
-            h = r & 1;
-            S = 2;
-        }
-        double g0 = 0.0, g1 = 0.0;
-        int b = 0;
-        if (t < ntask) {
-            b = gorder[1 + j];
-            int k = L.inc_off[b] + h;
-            const int k1 = L.inc_off[b + 1];
-            for (; k + S < k1; k += 2 * S) {
-                int e0 = L.inc_list[k], e1 = L.inc_list[k + S];
-                int r0 = e0 >> 1, r1 = e1 >> 1;
-                g0 += (double)L.rf(RJ + 6 * (e0 & 1) + c, r0) * ((double)vp[r0] * (double)x[r0]);
-                g1 += (double)L.rf(RJ + 6 * (e1 & 1) + c, r1) * ((double)vp[r1] * (double)x[r1]);
-            }
-            if (k < k1) {
-                int e0 = L.inc_list[k];
-                int r0 = e0 >> 1;
-                g0 += (double)L.rf(RJ + 6 * (e0 & 1) + c, r0) * ((double)vp[r0] * (double)x[r0]);
-            }
-        }
-        double gs = g0 + g1;
-        gs += dpp<kDppXor1>(gs);
-        const double g4 = gs + dpp<kDppXor2>(gs);
-        if (t < ntask && h == 0) L.wb[c * kMaxBodies + b] = heavy ? g4 : gs;
-    };
-    task(threadIdx.x);
-    for (int t0 = NT; t0 < ntask; t0 += NT) task(t0 + threadIdx.x);
-    __syncthreads();
+struct GatherTask {
+    int b, c, h, S;  // body, component, this thread's place among its S threads
+    int k, k1;       // its entries of the incidence list: k, k + S, ... below k1
+    bool heavy;
+};
+
+__device__ inline GatherTask gather_task(const Lds &L, int t, int nheavy, int ntask, int nh,
+                                         const unsigned char *gorder) {
+    GatherTask g;
+    g.heavy = t < nheavy;
+    int j;
+    if (g.heavy) {
+        j = t / 24;
+        const int r = t - 24 * j;
+        g.c = r >> 2;
+        g.h = r & 3;
+        g.S = 4;
+    } else {
+        const int u = t - nheavy, q = u / 12, r = u - 12 * q;
+        j = nh + q;
+        g.c = r >> 1;
+        g.h = r & 1;
+        g.S = 2;
+    }
+    g.b = g.k = g.k1 = 0;
+    if (t < ntask) {
+        g.b = gorder[1 + j];
+        g.k = L.inc_off[g.b] + g.h;
+        g.k1 = L.inc_off[g.b + 1];
+    }
+    return g;
+}
+
+// The entries of a task from k on, alternately into g0 and g1 (k lies an even
+// number of entries after the task's first); px holds p_r x_r in FP64 (exact:
+// two 24-bit factors).
+__device__ inline void gather_rest(const Lds &L, const GatherTask &t, int k, const double *px, double &g0, double &g1) {
+    for (; k + t.S < t.k1; k += 2 * t.S) {
+        int e0 = L.inc_list[k], e1 = L.inc_list[k + t.S];
+        int r0 = e0 >> 1, r1 = e1 >> 1;
+        g0 += (double)L.rf(RJ + 6 * (e0 & 1) + t.c, r0) * px[r0];
+        g1 += (double)L.rf(RJ + 6 * (e1 & 1) + t.c, r1) * px[r1];
+    }
+    if (k < t.k1) {
+        int e0 = L.inc_list[k];
+        int r0 = e0 >> 1;
+        g0 += (double)L.rf(RJ + 6 * (e0 & 1) + t.c, r0) * px[r0];
+    }
+}
+
+// The sums of a task's threads meet by lane exchanges; the first writes.
+__device__ inline void gather_store(const Lds &L, const GatherTask &t, bool on, double gs) {
+    gs += dpp<kDppXor1>(gs);
+    const double g4 = gs + dpp<kDppXor2>(gs);
+    if (on && t.h == 0) L.wb[t.c * kMaxBodies + t.b] = t.heavy ? g4 : gs;
+}
+
+// Rows of a gather task held in registers through the iterations; longer
+// lists read the rest from LDS.  The biped's longest list has 30 rows on four
+// threads.
+constexpr int kGatherRegs = 8;
+
+// acc (rows 0 and 2) and acc2 (rows 1 and 3) of X^T t for four rows; explicit
+// fused multiply-adds, so that every caller computes the same bits
+__device__ inline void x_accumulate(const mfx4 (&x)[4], mfx4 tv, mfx4 &acc, mfx4 &acc2) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = __builtin_fmaf(x[0][c], tv[0], acc[c]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc2[c] = __builtin_fmaf(x[1][c], tv[1], acc2[c]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = __builtin_fmaf(x[2][c], tv[2], acc[c]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc2[c] = __builtin_fmaf(x[3][c], tv[3], acc2[c]);
 }
 
 // w = M_b^-1 g_b in FP64 (body frame: R diag(I^-1) R^T for the angular part)
@@ -396,9 +498,12 @@ __device__ inline void delassus_apply(const Lds &L, int m, int nb, const float *
 // this out-of-line copy leaves that code and its schedule alone.  Returns
 // nonzero when a pivot is not positive.
 template <int MC, int NT>
-__device__ __attribute__((noinline)) int factor_invert_again(const Lds &L, float *A, int m, int *s_int,
-                                                             const StepArgs &a, int w) {
+__device__ __attribute__((noinline)) int factor_invert_again(int m) {
     const int tid = threadIdx.x;
+    const Lds L = lds_views<MC>();
+    float *A = L.A;
+    int *s_int = L.s_int;
+    m = uniform(m);
     // ---- Cholesky of D~ + diag(eta + rho), in place (Alg. 1 step 1):
     //      right-looking over 16x16 tiles.  Wave 0 factors a diagonal tile in
     //      registers (lane r holds row r) and forms its inverse; the panel
@@ -473,22 +578,10 @@ __device__ __attribute__((noinline)) int factor_invert_again(const Lds &L, float
                 if (I != J || fr <= rr) A[tri_row_offset(16 * I + rr) + 16 * J + fr] -= acc[c];
             }
         };
-#ifdef KAMX_FACTOR_TIMING
-        uint64_t fsub[4] = {0, 0, 0, 0}, fmark = a.phase_clk && tid == 0 ? wall_clock64() : 0;
-#define KAMX_FMARK(k)                                   \
-    if (a.phase_clk && tid == 0) {                      \
-        uint64_t now_ = wall_clock64();                 \
-        fsub[k] += now_ - fmark;                        \
-        fmark = now_;                                   \
-    }
-#else
-#define KAMX_FMARK(k)
-#endif
         if (wv == 0) factor_diag(0);
         __syncthreads();
-        KAMX_FMARK(0);
         for (int K = 0; K < T; ++K) {
-            if (s_int[2]) break;
+            if (uniform(s_int[2])) break;
             const int k0 = 16 * K;
             const int nI = T - K - 1;
             // panel: L_IK = A_IK Xkk^T for the tiles I below the diagonal,
@@ -503,7 +596,6 @@ __device__ __attribute__((noinline)) int factor_invert_again(const Lds &L, float
                 for (int c = 0; c < 4; ++c) A[tri_row_offset(16 * I + 4 * fk + c) + k0 + fr] = acc[c];
             }
             __syncthreads();
-            KAMX_FMARK(1);
             if (nI == 0) break;
             // trailing update A_IJ -= L_IK L_JK^T, K < J <= I.  Pair 0 is the
             // next diagonal tile: wave 0 updates and factors it; the other
@@ -522,18 +614,11 @@ __device__ __attribute__((noinline)) int factor_invert_again(const Lds &L, float
                 }
             }
             __syncthreads();
-            KAMX_FMARK(2);
         }
-#ifdef KAMX_FACTOR_TIMING
-        if (a.phase_clk && tid == 0)
-            for (int q = 0; q < 3; ++q) a.phase_clk[16 * w + 8 + q] = fsub[q];
-#endif
-#undef KAMX_FMARK
     }
     __syncthreads();
-    const int factor_fail = s_int[2];
+    const int factor_fail = uniform(s_int[2]);
 
-    if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 4] = wall_clock64();
     // ---- explicit inverse of the factor, in place: X = L^-1 over 16x16
     //      tiles.  Diagonal tiles are inverted in registers (one wave per
     //      tile); then tile row by tile row, M_ik = X_ii L_ik (k < i) and
@@ -632,9 +717,13 @@ __device__ __attribute__((noinline)) int factor_invert_again(const Lds &L, float
 // (the vector region that held W now holds the iterates).  Uses the
 // reduction area (free between iterations) for the pair-task offsets.
 template <int MC, int NT>
-__device__ __attribute__((noinline)) void reassemble(const Lds &L, float *A, int m, int nb, const float *vp,
-                                                     const float *vrho, float eta) {
+__device__ __attribute__((noinline)) void reassemble(int m, int nb, float eta) {
     const int tid = threadIdx.x;
+    const Lds L = lds_views<MC>();
+    float *A = L.A;
+    const float *vp = L.vec(VP), *vrho = L.vec(VRHO);
+    m = uniform(m);
+    nb = uniform(nb);
     const int Mp = (m + 15) & ~15;
     const int n4 = tri_row_offset(Mp) >> 2;
     for (int k = tid; k < n4; k += NT) reinterpret_cast<float4 *>(A)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -702,30 +791,563 @@ __device__ __attribute__((noinline)) void reassemble(const Lds &L, float *A, int
     __syncthreads();
 }
 
-template <int MC, int NT>
-__device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, int *s_int) {
-    extern __shared__ float4 smem4[];
-    float *sm = reinterpret_cast<float *>(smem4);
-    const int tid = threadIdx.x;
-    // read per step (not hoisted out of the caller's step loop)
-    const int w = a.bucket_worlds[blockIdx.x];
-    const uint32_t step = *a.step_ctr + (uint32_t)k;
-    const WorldInfo W = a.worlds[w];
-    const SolverParams &P = a.p;
+constexpr int kSolveConverged = 1 << 8;  // beside the KAMX_WORLD bits in solve_pass's status
 
-    Lds L;
-    L.mc = MC;
-    L.b = sm;
-    L.j = L.b + body_floats();
-    L.c = L.j + joint_floats();
-    L.r = L.c + contact_floats();
-    L.v = L.r + row_floats(MC);
-    L.A = L.v + vec_floats(MC);
-    L.red = L.A + tri_row_offset(MC);
-    L.wb = reinterpret_cast<double *>(L.red + 64);
-    L.qd = L.wb + 6 * kMaxBodies;
-    L.inc_off = reinterpret_cast<int *>(L.red + 64 + bodyw_floats() + posed_floats());
-    L.inc_list = L.inc_off + kMaxBodies + 1;
+// One pass of the PADMM iteration (Alg. 1 steps 3-10) from iteration it on, with
+// the factor inverse X in the triangle: until the solve exits (returns 0) or the
+// adaptive penalty wants rho changed (returns the direction).  The x-update of
+// step 5 is computed as x + X^T X (rhs - (D~ + eta + rho) x): one refinement step
+// from the previous iterate with the FP32 factor inverse and an FP64 matrix-free
+// residual, so the fixed point solves the linear system to the accuracy of the
+// residual, not to cond(D~) times FP32 epsilon.
+//
+// Out of line, so that the registers of its loop are its own.  Hands over, in
+// s_int: [4] the next iteration, [5] status bits and kSolveConverged, [6..8] r_p,
+// r_d, r_c; the iterates x, y, z (and y, z as the extrapolated ones) and D~ x in
+// their fields.
+//
+// An iteration is a chain of short phases between barriers, each bound by the
+// latency of the LDS reads it starts with, so whatever a thread reads in every
+// iteration stays in its registers for the pass (its entries of X for the x
+// update, its rows of the body gather, its row's Jacobian and M^-1, its block's
+// iterates) and a phase is left with one round of LDS reads of what other threads
+// wrote, all issued before the first is used.  On the biped (224 rows, one world
+// of eight waves per compute unit) an iteration takes 3.0 us against 5.2 us with
+// every operand read from LDS where it is used.
+template <int MC, int NT>
+__device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int m, int nb, int nc, int row_c0,
+                                                    int nlim, int it) {
+    const int tid = threadIdx.x;
+    KernelArgs &a = *uniform_args(args);
+    SolverArgs &P = a.p;
+    w = uniform(w);
+    m = uniform(m);
+    nb = uniform(nb);
+    nc = uniform(nc);
+    row_c0 = uniform(row_c0);
+    it = uniform(it);
+    const int n_uni = uniform(nlim) + 3 * nc;  // limit and contact rows: what the adaptive penalty acts on
+    const Lds L = lds_views<MC>();
+    const float *A = L.A;
+    float *vp = L.vec(VP), *vrho = L.vec(VRHO), *vvt = L.vec(VVT);
+    float *vx = L.vec(VX), *vyh = L.vec(VYH), *vzh = L.vec(VZH), *vyp = L.vec(VYP), *vzp = L.vec(VZP);
+    float *vrhs = L.vec(VRHS), *vt = L.t, *vxn = L.vec(VXN), *vrinv = L.vec(VCOL), *vdx = L.vec(VDX);
+    // p x per row in FP64, over the warm-start and aux fields
+    double *px = reinterpret_cast<double *>(L.vec(VWS));
+    static_assert(VAUX == VWS + 1 && (VWS * MC) % 2 == 0, "MC doubles in two adjacent fields");
+    const mfx4 kZero4 = {0.f, 0.f, 0.f, 0.f};
+    const float eta = P.eta, eps = P.eps, restart_factor = P.restart_factor, adapt_ratio = P.adapt_ratio;
+    const int fixed_iters = P.fixed_iters, max_iters = P.max_iters, accel = P.accel;
+    const int N = fixed_iters > 0 ? fixed_iters : max_iters;
+    // the next checkpoint of the adaptive penalty (adapt_first, then doubling; -1: none)
+    int check = -1;
+    if (adapt_ratio > 0.f && n_uni > 0 && P.adapt_first > 0)
+        for (check = P.adapt_first; check < it; check = check < (1 << 29) ? 2 * check : 0x7fffffff) {}
+
+    // ---- gather balance: bodies with more than half the longest incidence
+    // list go first and take four threads per component, as far as
+    // 12 (nb + nh) <= T allows for the bucket's default workgroup size T (the
+    // same bodies, so the same sums, at every size: a four-thread body adds its
+    // rows in another order than a two-thread one); the order is bytes in the
+    // reduction area, behind the partial sums.  Wave 0 builds it, lane b for body
+    // b: a wave max, then ranks from ballots.
+    static_assert(kMaxBodies <= 64, "gather order: one lane per body");
+    unsigned char *gorder = reinterpret_cast<unsigned char *>(L.red + 36);
+    float *zero4 = L.red + 60;  // four zeros, read in place of entries a thread does not have
+    if (tid < 64) {
+        const int kb = tid < nb ? L.inc_off[tid + 1] - L.inc_off[tid] : 0;
+        int kmax = kb;
+        for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
+        const unsigned long long below = (1ull << tid) - 1ull;
+        const unsigned long long hv = __ballot(tid < nb && 2 * kb > kmax);
+        constexpr int kGatherThreads = default_bucket_threads(MC);
+        static_assert(kGatherThreads >= 64, "gather cap from the bucket's default size");
+        const int cap = max(kGatherThreads / 12 - nb, 0);
+        const bool heavy = ((hv >> tid) & 1ull) && __popcll(hv & below) < cap;
+        const unsigned long long hm = __ballot(heavy);
+        const int nh = __popcll(hm);
+        if (tid < nb) gorder[1 + (heavy ? __popcll(hm & below) : nh + tid - __popcll(hm & below))] = (unsigned char)tid;
+        if (tid == 0) gorder[0] = (unsigned char)nh;
+        if (tid < 4) zero4[tid] = 0.f;
+    }
+    __syncthreads();
+    const int gnh = uniform((int)gorder[0]);
+
+    // ---- slots of X (4 rows of a column quad) for the x update: quads c and
+    // Q-1-c form a pair (balanced: together they span m + 4 rows), 16 threads per
+    // pair take every 16th group of 4 rows.  kX1 slots cover the pair's first
+    // quad and kX2 its second, which starts at or below the middle.  A wave's
+    // pairs g0 .. g0 + 3 take kX1 slots of the first only when g0 is small and
+    // kX2 = 2 of the second only when g0 >= 16, so the last of both share one.
+    constexpr int kX1 = (MC + 63) / 64, kX2 = (MC / 2 + 63) / 64;
+    static_assert(kX2 == 1 || (kX2 == 2 && MC / 4 - 16 * (kX1 - 1) <= 16), "shared slot of the x update");
+    constexpr int kOwn1 = kX2 == 2 ? kX1 - 1 : kX1;  // slots of the first quad alone
+    constexpr int kXSlots = kOwn1 + 1 + (kX2 == 2 ? 1 : 0);
+    const int Q = (m + 3) >> 2, g0 = tid >> 4, kq = tid & 15;
+    const bool b3 = kq & 8, b2 = kq & 4, b1 = kq & 2;
+    const int c1 = g0, c2 = Q - 1 - g0;
+    const bool one = c1 <= c2, two = c1 < c2;  // the pair has a first, a second quad
+    const bool share1 = kX2 == 1 || uniform(g0) < 16;
+    mfx4 X[kXSlots][4];
+    // t of the slots' rows: t is 0 from row m to the end of its field, past the
+    // last slot's last row
+    const float *xt1 = vt + 4 * (min(c1, MC / 8) + kq), *xt2 = vt + 4 * (min(max(c2, 0), MC / 4) + kq);
+    {
+        auto load = [&](mfx4 (&x)[4], bool on, int c, int q) {
+            const int r = 4 * (c + kq) + 64 * q;
+            on = on && r < m;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                x[e] = on ? *reinterpret_cast<const mfx4 *>(A + tri_row_offset(r + e) + 4 * c) : kZero4;
+        };
+#pragma unroll
+        for (int q = 0; q < kOwn1; ++q) load(X[q], one, c1, q);
+        load(X[kOwn1], two, c2, 0);
+        if (kX2 == 2) {
+            if (share1) load(X[kXSlots - 1], one, c1, kX1 - 1);
+            else load(X[kXSlots - 1], two, c2, 1);
+        }
+    }
+    // the row this lane's sum of a t or x pass belongs to (-1: none): the eight
+    // sums of a pair are reduce-scattered over its 16 lanes
+    int prow = 4 * (b3 ? c2 : c1) + (b2 ? 2 : 0) + (b1 ? 1 : 0);
+    if ((kq & 1) || !one || (b3 && !two) || prow >= m) prow = -1;
+    float xw = 0.f, xp = 0.f;  // x and p of that row
+    if (prow >= 0) {
+        xw = vx[prow];
+        xp = vp[prow];
+    }
+    // sums over the 16 lanes of a pair: halve the eight at each exchange (row
+    // mirror, half-row mirror, then pairs), so that lanes 2k and 2k+1 end with
+    // sum 4 b3 + 2 b2 + b1 of the bits of k
+    auto pair_sums = [&](const mfx4 &s1, const mfx4 &s2) {
+        const float v8[8] = {s1[0], s1[1], s1[2], s1[3], s2[0], s2[1], s2[2], s2[3]};
+        float u4[4], u2[2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            u4[k] = (b3 ? v8[k + 4] : v8[k]) + dpp<kDppMirror16>(b3 ? v8[k] : v8[k + 4]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) u2[k] = (b2 ? u4[k + 2] : u4[k]) + dpp<kDppMirror8>(b2 ? u4[k] : u4[k + 2]);
+        float z = (b1 ? u2[1] : u2[0]) + dpp<kDppXor2>(b1 ? u2[0] : u2[1]);
+        z += dpp<kDppXor1>(z);
+        return z;
+    };
+
+    // ---- gather: this thread's first task, its first kGatherRegs rows' J and
+    // the places of their p x
+    const int gnheavy = 24 * gnh, gntask = gnheavy + 12 * (nb - gnh);
+    const GatherTask gt = gather_task(L, tid, gnheavy, gntask, gnh, gorder);
+    float gJ[kGatherRegs];
+    const double *gx[kGatherRegs];
+#pragma unroll
+    for (int q = 0; q < kGatherRegs; ++q) {
+        const int k = gt.k + q * gt.S;
+        gJ[q] = 0.f;
+        gx[q] = reinterpret_cast<const double *>(zero4);
+        if (k < gt.k1) {
+            const int e = L.inc_list[k];
+            gJ[q] = L.rf(RJ + 6 * (e & 1) + gt.c, e >> 1);
+            gx[q] = px + (e >> 1);
+        }
+    }
+    const int grest = gt.k + kGatherRegs * gt.S;
+
+    // ---- row io = tid / 2 belongs to the lane pair (2 io, 2 io + 1): the pair
+    // evaluates the row's matrix-free product (even lane body a's side, odd lane
+    // body b's), and the even lane of a block's first row owns the block, so
+    // owner work spreads over every wave
+    const int io = tid >> 1, hh = tid & 1;
+    const int kind_o = io < m ? L.ri(RKIND, io) : -1;
+    const bool owner_o = io < m && kind_o != kRowTangent && hh == 0;
+    const bool normal_o = owner_o && kind_o == kRowNormal;
+    const int blk_o = kind_o == kRowNormal ? 3 : 1;
+    const float mu_o = io < m ? L.rf(RMU, io) : 0.f;
+    const float cone_o = hw_rcp(1.f + mu_o * mu_o);
+    int sb = -1;
+    float sJ[6], sim = 0.f, spr = 0.f, sreg = 0.f;
+    double sM[6];
+    for (int c = 0; c < 6; ++c) {
+        sJ[c] = 0.f;
+        sM[c] = 0.0;
+    }
+    if (io < m) {
+        sb = hh == 0 ? L.ri(RIA, io) : L.ri(RIB, io);
+        spr = vp[io];
+        sreg = L.rf(RREG, io);
+        for (int c = 0; c < 6; ++c) sJ[c] = L.rf(RJ + 6 * hh + c, io);
+        if (sb >= 0) {
+            const double *mi = reinterpret_cast<const double *>(L.b);
+            for (int c = 0; c < 6; ++c) sM[c] = mi[c * kMaxBodies + sb];
+            sim = L.bf(BIM, sb);
+        }
+    }
+    const double *sg = L.wb + (sb >= 0 ? sb : 0);
+    const float *sx = io < m ? vxn + io : zero4;
+    // whether this wave has a contact's owner, and whether some contact's rows
+    // lie in two waves (32 rows to a wave)
+    const bool wave_contact = __ballot(normal_o) != 0;
+    bool straddle = false;
+    for (int c = 0; c < nc; ++c) straddle = straddle || ((row_c0 + 3 * c) & 31) > 29;
+
+    // ---- block owners: iterates, free velocity and penalty (the same in all
+    // rows of a block)
+    float oyh[3], ozh[3], oyp[3], ozp[3], ovt[3], ox[3], odx[3];
+    const float orho = owner_o ? vrho[io] : 1.f, ori = owner_o ? vrinv[io] : 1.f;
+    _Pragma("unroll") for (int e = 0; e < 3; ++e) {
+        const bool on = owner_o && e < blk_o;
+        oyh[e] = on ? vyh[io + e] : 0.f;
+        ozh[e] = on ? vzh[io + e] : 0.f;
+        oyp[e] = on ? vyp[io + e] : 0.f;
+        ozp[e] = on ? vzp[io + e] : 0.f;
+        ovt[e] = on ? vvt[io + e] : 0.f;
+        ox[e] = on ? vx[io + e] : 0.f;
+        odx[e] = on ? vdx[io + e] : 0.f;
+    }
+    // steps 4-5: rhs = -v~_f - Gamma(z^) + eta x + rho y^ + z^, and its residual
+    // against the current x
+    auto put_rhs = [&]() {
+        if (owner_o) {
+            const float s_own = kind_o == kRowNormal ? mu_o * hw_sqrt(ozh[1] * ozh[1] + ozh[2] * ozh[2]) : 0.f;
+            _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
+                float rhs = -ovt[e] - (e == 0 ? s_own : 0.f) + eta * ox[e] + orho * oyh[e] + ozh[e];
+                vrhs[io + e] = rhs - (odx[e] + (eta + orho) * ox[e]);
+            }
+        }
+    };
+    put_rhs();
+
+    float a_k = 1.f, c_prev = INFINITY;
+    float rp = 0.f, rd = 0.f, rc = 0.f;
+    if (it > 1) {  // a pass without an iteration leaves the previous one's residuals
+        rp = __int_as_float(uniform(L.s_int[6]));
+        rd = __int_as_float(uniform(L.s_int[7]));
+        rc = __int_as_float(uniform(L.s_int[8]));
+    }
+    int adapt_pending = 0, status = 0;
+    const int it0 = it;
+    const bool timing = a.phase_clk != nullptr;
+    uint64_t sub[6] = {0, 0, 0, 0, 0, 0}, tmark = 0;
+#define KAMX_MARK(k)                                             \
+    if (timing) {                                                \
+        uint64_t now_ = wall_clock64();                          \
+        if ((k) > 0) sub[(k) > 0 ? (k) - 1 : 0] += now_ - tmark; \
+        tmark = now_;                                            \
+    }
+    for (; it <= N; ++it) {
+        KAMX_MARK(0);
+        __syncthreads();
+        KAMX_MARK(1);
+        // t = X r over groups of 4 rows: groups g and Q-1-g form a pair
+        // (balanced: together they span Q+1 column quads); 16 threads per pair
+        // take every 16th column quad, reading the quad of r once for the 4 rows
+        // of a group.  The rows of a group lie back to back, 4(G+1) floats apart;
+        // the pads of the diagonal quad hold 0 and r is 0 past row m, and rows
+        // past m (up to the next multiple of 16) hold finite values whose sums are
+        // not stored.  Two quads' reads are in flight at a time; a lane past its
+        // group's last quad reads that quad against zeros.
+        {
+            int to = tid;
+            asm volatile("" : "+v"(to));  // addresses formed here, not held through the loop
+            const int gg = to >> 4, kk = to & 15;
+            const int G1 = gg, G2 = max(Q - 1 - gg, 0);
+            const float *R1 = A + tri_row_offset(4 * G1), *R2 = A + tri_row_offset(4 * G2);
+            mfx4 s1 = kZero4, s2 = kZero4;
+            struct Chunk {
+                mfx4 r, x[4];
+            };
+            auto read = [&](Chunk &h, const float *R, int G, int q) {
+                const int c = kk + 16 * q, cc = min(c, G);
+                h.r = *reinterpret_cast<const mfx4 *>(c <= G ? vrhs + 4 * c : zero4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    h.x[e] = *reinterpret_cast<const mfx4 *>(R + 4 * e * (G + 1) + 4 * cc);
+            };
+            auto add = [&](const Chunk &h, mfx4 &s) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) s[k] = __builtin_fmaf(h.x[k][e], h.r[e], s[k]);
+            };
+            constexpr int kT1 = (MC / 8 + 15) / 16, kT2 = (MC / 4 + 15) / 16;
+            static_assert(kT1 <= 2 && kT2 <= 4 && kT2 >= kT1, "chunks of a t-pass pair");
+            // chunks a wave needs: its largest first and second group
+            const int gw = uniform(gg);
+            const int n1 = min((gw + 3) / 16 + 1, kT1), n2 = (max(Q - 1 - gw, 0)) / 16 + 1;
+            if constexpr (kT2 <= 2) {
+                // small worlds: every read in flight
+                Chunk ha, hb;
+                read(hb, R2, G2, 0);
+                read(ha, R1, G1, 0);
+                add(hb, s2);
+                add(ha, s1);
+                if (kT2 > 1 && n2 > 1) {
+                    read(hb, R2, G2, 1);
+                    add(hb, s2);
+                }
+                static_assert(kT2 > 2 || kT1 == 1, "first groups of small worlds fit one chunk");
+            } else {
+                // large ones have the waves to overlap and no registers to spare
+                Chunk h;
+#pragma clang loop unroll(disable)
+                for (int q = 0; q < n2; ++q) {
+                    read(h, R2, G2, q);
+                    add(h, s2);
+                }
+#pragma clang loop unroll(disable)
+                for (int q = 0; q < n1; ++q) {
+                    read(h, R1, G1, q);
+                    add(h, s1);
+                }
+            }
+            const float z = pair_sums(s1, s2);
+            if (prow >= 0) vt[prow] = z;
+        }
+        __syncthreads();
+        KAMX_MARK(2);
+        // x_new = x + X^T t: every slot's t against its X in registers (packed
+        // rows are padded to 4 floats and the pads hold 0, so the quad that
+        // contains the diagonal enters as-is, and t is 0 past row m, where the
+        // rows up to the next multiple of 4 hold finite values)
+        {
+            mfx4 s1 = kZero4, s2 = kZero4, o1 = kZero4, o2 = kZero4;
+            mfx4 tv[kXSlots];
+#pragma unroll
+            for (int q = 0; q < kOwn1; ++q) tv[q] = *reinterpret_cast<const mfx4 *>(xt1 + 64 * q);
+            tv[kOwn1] = *reinterpret_cast<const mfx4 *>(xt2);
+            if (kX2 == 2) tv[kXSlots - 1] = *reinterpret_cast<const mfx4 *>(share1 ? xt1 + 64 * (kX1 - 1) : xt2 + 64);
+#pragma unroll
+            for (int q = 0; q < kOwn1; ++q) x_accumulate(X[q], tv[q], s1, o1);
+            x_accumulate(X[kOwn1], tv[kOwn1], s2, o2);
+            if (kX2 == 2) {
+                if (share1) x_accumulate(X[kXSlots - 1], tv[kXSlots - 1], s1, o1);
+                else x_accumulate(X[kXSlots - 1], tv[kXSlots - 1], s2, o2);
+            }
+            s1 += o1;
+            s2 += o2;
+            const float z = pair_sums(s1, s2);
+            if (prow >= 0) {
+                xw = xw + z;
+                vxn[prow] = xw;
+                px[prow] = (double)xp * (double)xw;
+            }
+        }
+        __syncthreads();
+        KAMX_MARK(3);
+        // v~ - v~_f = D~ x_new (matrix-free, FP64): bodies gather here, the rows
+        // read their two bodies below
+        {
+            double s0 = 0.0, s1 = 0.0, xv[kGatherRegs];
+#pragma unroll
+            for (int q = 0; q < kGatherRegs; ++q) xv[q] = *gx[q];
+#pragma unroll
+            for (int q = 0; q < kGatherRegs; q += 2) {
+                s0 += (double)gJ[q] * xv[q];
+                s1 += (double)gJ[q + 1] * xv[q + 1];
+            }
+            gather_rest(L, gt, grest, px, s0, s1);
+            gather_store(L, gt, tid < gntask, s0 + s1);
+            // (only when the tasks outnumber the threads)
+            for (int t0 = NT; t0 < gntask; t0 += NT) {
+                const GatherTask g = gather_task(L, t0 + tid, gnheavy, gntask, gnh, gorder);
+                s0 = s1 = 0.0;
+                gather_rest(L, g, g.k, px, s0, s1);
+                gather_store(L, g, t0 + tid < gntask, s0 + s1);
+            }
+        }
+        __syncthreads();
+        KAMX_MARK(4);
+        // v~ - v~_f of row io in FP64: J_a M_a^-1 g_a on the even lane,
+        // J_b M_b^-1 g_b on the odd lane, added by the pair sum (M^-1 as in
+        // body_minv64)
+        float yb[3], zb[3];
+        float dxo;
+        {
+            double side = 0.0, g[6], wv[6];
+            for (int c = 0; c < 6; ++c) g[c] = sg[c * kMaxBodies];
+            ox[0] = *sx;
+            if (wave_contact) {
+                ox[1] = sx[1];
+                ox[2] = sx[2];
+            }
+            for (int c = 0; c < 3; ++c) wv[c] = g[c] * (double)sim;
+            wv[3] = __builtin_fma(sM[4], g[5], __builtin_fma(sM[3], g[4], sM[0] * g[3]));
+            wv[4] = __builtin_fma(sM[5], g[5], __builtin_fma(sM[1], g[4], sM[3] * g[3]));
+            wv[5] = __builtin_fma(sM[2], g[5], __builtin_fma(sM[5], g[4], sM[4] * g[3]));
+            for (int c = 0; c < 6; ++c) side += (double)sJ[c] * wv[c];
+            side = sb >= 0 ? side : 0.0;
+            side = lane_group_sum<2>(side);
+            const double pr = (double)spr;
+            dxo = (float)((side + (double)sreg * pr * (double)ox[0]) * pr);
+        }
+        // a contact's tangent rows belong to the next two lane pairs, which hand
+        // their rows to the owner: by lane exchange, or through LDS where some
+        // contact lies in two waves
+        odx[0] = dxo;
+        if (straddle) {
+            if (hh == 0 && io < m) vdx[io] = dxo;
+            __syncthreads();
+            if (normal_o) {
+                odx[1] = vdx[io + 1];
+                odx[2] = vdx[io + 2];
+            }
+        } else if (wave_contact) {
+            odx[1] = __shfl_down(dxo, 2);
+            odx[2] = __shfl_down(dxo, 4);
+        }
+        // steps 6-7 and the residuals of step 9 (block owners)
+        float lrp = 0.f, lrd = 0.f, lrc = 0.f, lcc = 0.f;
+        if (owner_o) {
+            float vv[3];
+            _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) vv[e] = odx[e] + ovt[e];
+            if (kind_o == kRowNormal) {
+                // the cone's three cases as selections (proj_cone's values)
+                const float w0 = ox[0] - ozh[0] * ori, w1 = ox[1] - ozh[1] * ori, w2 = ox[2] - ozh[2] * ori;
+                const float tn = hw_sqrt(w1 * w1 + w2 * w2);
+                const float mt = mu_o * tn, ln = add_rounded(mt, w0) * cone_o;
+                const float sc = tn > 0.f ? mu_o * ln * hw_rcp(tn) : 0.f;
+                const bool in = tn <= mu_o * w0, below = mt <= -w0;
+                yb[0] = in ? w0 : (below ? 0.f : ln);
+                yb[1] = in ? w1 : (below ? 0.f : sc * w1);
+                yb[2] = in ? w2 : (below ? 0.f : sc * w2);
+            } else if (kind_o == kRowLimit) {
+                yb[0] = fmaxf(ox[0] - ozh[0] * ori, 0.f);
+            } else {
+                yb[0] = ox[0] - ozh[0] * ori;
+            }
+            _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
+                zb[e] = ozh[e] - orho * (ox[e] - yb[e]);
+                lrp = fmaxf(lrp, fabsf(ox[e] - yb[e]));
+                float dy = yb[e] - oyh[e], dz = zb[e] - ozh[e];
+                lcc += orho * dy * dy + dz * dz * ori;
+            }
+            float g = kind_o == kRowNormal ? mu_o * hw_sqrt(vv[1] * vv[1] + vv[2] * vv[2]) : 0.f;
+            _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
+                float d = vv[e] + (e == 0 ? g : 0.f) - zb[e];
+                lrd = fmaxf(lrd, fabsf(d));
+                if (d != d) lrd = fabsf(d);
+            }
+            if (kind_o == kRowNormal) lrc = fabsf(yb[0] * (vv[0] + g) + yb[1] * vv[1] + yb[2] * vv[2]);
+            else if (kind_o == kRowLimit) lrc = fabsf(yb[0] * vv[0]);
+            if (lrp != lrp || lcc != lcc) lrp = NAN;
+        }
+        // step 8's next Nesterov weights, before the reduction that decides on them
+        const float a_next = 0.5f * (1.f + hw_sqrt(1.f + 4.f * a_k * a_k));
+        const float beta = (a_k - 1.f) * hw_rcp(a_next), c_most = restart_factor * c_prev;
+        // every iteration needs the restart sum and whether all residuals are
+        // finite and below eps: their largest.  Each for itself is reduced only
+        // where it is read
+        float rmax = max_nonneg(max_nonneg(lrp, lrd), lrc), csum = lcc;
+        reduce_max_sum<NT>(rmax, csum, L.red);
+        KAMX_MARK(5);
+        // step 8: Nesterov with adaptive restart
+        const bool restart = accel && !(csum < c_most);
+        if (!accel || !restart) {
+            if (accel) {
+                a_k = a_next;
+                c_prev = csum;
+            }
+            if (owner_o) {
+                _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
+                    oyh[e] = accel ? yb[e] + beta * (yb[e] - oyp[e]) : yb[e];
+                    ozh[e] = accel ? zb[e] + beta * (zb[e] - ozp[e]) : zb[e];
+                }
+            }
+        } else {
+            a_k = 1.f;
+            c_prev = c_prev / restart_factor;
+            _Pragma("unroll") for (int e = 0; e < 3; ++e) {
+                oyh[e] = oyp[e];
+                ozh[e] = ozp[e];
+            }
+        }
+        if (owner_o) {
+            _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
+                oyp[e] = yb[e];
+                ozp[e] = zb[e];
+            }
+        }
+        put_rhs();
+        KAMX_MARK(6);
+        // adaptive penalty (not in the paper: residual balancing) at the
+        // checkpoints of a solve that does not exit here; every value here is
+        // uniform
+        const bool done = fixed_iters <= 0 && rmax < eps;
+        int adapt_dir = 0;
+        if (it == N || it == check || done || !isfinite(rmax)) {
+            __syncthreads();  // every wave has read the partial results
+            reduce4<NT>(lrp, lrd, lrc, lcc, L.red);
+            rp = uniform(lrp);
+            rd = uniform(lrd);
+            rc = uniform(lrc);
+            if (it == check) {
+                check = check < (1 << 29) ? 2 * check : 0x7fffffff;
+                if (!done) {
+                    if (rd > adapt_ratio * rp) adapt_dir = 1;
+                    else if (rp > adapt_ratio * rd) adapt_dir = 2;
+                }
+            }
+        }
+        if (tid == 0 && a.rlog && P.log_restarts && it <= max_iters)
+            a.rlog[(size_t)w * max_iters + (it - 1)] = (uint8_t)((restart ? 1 : 0) | (adapt_dir << 1));
+        if (!isfinite(rmax)) {
+            status = KAMX_WORLD_NONFINITE;
+            break;
+        }
+        if (done) {
+            status = kSolveConverged;
+            break;
+        }
+        if (adapt_dir) {
+            adapt_pending = adapt_dir;
+            ++it;
+            break;
+        }
+    }
+#undef KAMX_MARK
+    // the owners' iterates back to LDS, for the outputs and the next pass
+    if (owner_o) {
+        _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
+            vx[io + e] = ox[e];
+            vyp[io + e] = oyp[e];
+            vzp[io + e] = ozp[e];
+            vdx[io + e] = odx[e];
+            vyh[io + e] = oyp[e];
+            vzh[io + e] = ozp[e];
+        }
+    }
+    if (tid == 0) {
+        if (timing)
+            for (int k = 0; k < 6; ++k)
+                a.phase_clk[16 * w + 8 + k] = (it0 > 1 ? a.phase_clk[16 * w + 8 + k] : 0) + sub[k];
+        L.s_int[4] = it;
+        L.s_int[5] = status;
+        L.s_int[6] = __float_as_int(rp);
+        L.s_int[7] = __float_as_int(rd);
+        L.s_int[8] = __float_as_int(rc);
+    }
+    __syncthreads();
+    return adapt_pending;
+}
+
+template <int MC, int NT>
+__device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
+    const int tid = threadIdx.x;
+    KernelArgs &a = *uniform_args(args);
+    k = uniform(k);
+    // read per step (not hoisted out of the caller's step loop)
+    const int w = uniform(a.bucket_worlds[blockIdx.x]);
+    const uint32_t step = (uint32_t)uniform((int)*a.step_ctr) + (uint32_t)k;
+    WorldInfo W;
+    {
+        const int32_t *src = reinterpret_cast<const int32_t *>(a.worlds + w);
+        int32_t *dst = reinterpret_cast<int32_t *>(&W);
+#pragma unroll
+        for (int e = 0; e < (int)(sizeof(WorldInfo) / 4); ++e) dst[e] = uniform(src[e]);
+    }
+    SolverArgs &P = a.p;
+
+    const Lds L = lds_views<MC>();
+    int *s_int = L.s_int;
     float *A = L.A;
 
     const int nb = W.nb, nj = W.nj;
@@ -746,7 +1368,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
         if (rs && a.stage == 0) a.reset_count[w] += 1;
     }
     __syncthreads();
-    const int reset = s_int[0];
+    const int reset = uniform(s_int[0]);
 
     // ---- bodies: state, rotation, inverse mass properties
     for (int b = tid; b < nb; b += NT) {
@@ -856,7 +1478,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
     //      features are row 0 of the 16-row operand, the other rows zero.
     //      The triangle region of LDS is free until the Delassus assembly.
     if (P.warmstart == KAMX_WARM_LEARNED && !reset) {
-        const MlpView &N = a.mlp;
+        const __attribute__((address_space(4))) MlpView &N = a.mlp;
         __bf16 *xh = reinterpret_cast<__bf16 *>(A);
         __bf16 *h1 = xh + N.fp;
         __bf16 *h2 = h1 + N.H;
@@ -1012,7 +1634,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
         }
     }
     __syncthreads();
-    const int nc = s_int[1];
+    const int nc = uniform(s_int[1]);
     const int row_lim0 = 5 * nj;
     const int row_drv0 = 5 * nj + W.nlim;
     const int row_c0 = row_drv0 + W.ndrv;
@@ -1160,7 +1782,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
     //      row for bilateral and limit rows, one scalar per contact block
     const int i = tid;
     float *vp = L.vec(VP), *vrho = L.vec(VRHO), *vvt = L.vec(VVT);
-    float *tdiag = L.vec(VCOL), *tp = L.vec(VAUX);  // free fields above W
+    float *tdiag = L.vec(VCOL), *tp = L.vec(VDX);  // free fields above W
     const int kind_row = i < m ? L.ri(RKIND, i) : -1;
     if (i < m) {
         float dsum = L.rf(RREG, i);  // D_ii = J_i M^-1 J_i^T + R_ii
@@ -1242,6 +1864,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
     // the vector region held W and the scales until now: clear it (pads must
     // read as 0), then store P, rho and v~_f = P (J u_f + v*)
     for (int k = tid; k < vec_floats(MC); k += NT) L.v[k] = 0.f;
+    for (int k = tid; k < t_floats(MC); k += NT) L.t[k] = 0.f;
     __syncthreads();
     if (i < m) {
         vp[i] = pi_reg;
@@ -1259,8 +1882,11 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
     // ---- warm start (Alg. 1 step 2; Sec. 4.1): y = x = Pi_K(lambda_ws / p),
     //      z = v~(y) + Gamma(v~(y)) on unilateral rows, 0 on bilateral rows
     float *vx = L.vec(VX), *vyh = L.vec(VYH), *vzh = L.vec(VZH), *vyp = L.vec(VYP), *vzp = L.vec(VZP);
-    float *vrhs = L.vec(VRHS), *vt = L.vec(VT), *vxn = L.vec(VXN), *vws = L.vec(VWS), *vaux = L.vec(VAUX);
+    float *vrhs = L.vec(VRHS), *vxn = L.vec(VXN), *vws = L.vec(VWS), *vaux = L.vec(VAUX);
     float *vrinv = L.vec(VCOL), *vdx = L.vec(VDX);  // vrinv: 1/rho per row inside the iteration loop
+    // p x per row in FP64 inside the iteration loop, over the warm-start and aux fields
+    double *px = reinterpret_cast<double *>(vws);
+    static_assert(VAUX == VWS + 1 && (VWS * MC) % 2 == 0, "MC doubles in two adjacent fields");
     const int wmode = reset ? KAMX_WARM_COLD : P.warmstart;
     const int kind_i = i < m ? L.ri(RKIND, i) : -1;
     const bool owner = i < m && kind_i != kRowTangent;
@@ -1424,7 +2050,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
         __syncthreads();
         KAMX_FMARK(0);
         for (int K = 0; K < T; ++K) {
-            if (s_int[2]) break;
+            if (uniform(s_int[2])) break;
             const int k0 = 16 * K;
             const int nI = T - K - 1;
             // panel: L_IK = A_IK Xkk^T for the tiles I below the diagonal,
@@ -1467,7 +2093,7 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
 #undef KAMX_FMARK
     }
     __syncthreads();
-    const int factor_fail = s_int[2];
+    const int factor_fail = uniform(s_int[2]);
 
     if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 4] = wall_clock64();
     // ---- explicit inverse of the factor, in place: X = L^-1 over 16x16
@@ -1567,22 +2193,9 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
     //      to the accuracy of the residual, not to cond(D~) times FP32 epsilon.
     const float eta = P.eta;
     const float mu_i = i < m ? L.rf(RMU, i) : 0.f;
-    // Inside the iteration loop row io = tid / 2 belongs to the lane pair
-    // (2 io, 2 io + 1): the pair evaluates the row's matrix-free product
-    // (even lane body a's side, odd lane body b's), and the even lane of a
-    // block's first row owns the block, so owner work spreads over every
-    // wave and a contact's three rows go to three pairs.
-    const int io = tid >> 1, hh = tid & 1;
-    const int kind_o = io < m ? L.ri(RKIND, io) : -1;
-    const bool owner_o = io < m && kind_o != kRowTangent && hh == 0;
-    const int blk_o = kind_o == kRowNormal ? 3 : 1;
-    float rho_o = io < m ? vrho[io] : 1.f;  // changes only with the adaptive penalty
-    const float mu_o = io < m ? L.rf(RMU, io) : 0.f;
-    float a_k = 1.f, c_prev = INFINITY;
     int it = 0, status = 0;
     float rp = 0.f, rd = 0.f, rc = 0.f, rncp = 0.f;
     const int N = P.fixed_iters > 0 ? P.fixed_iters : P.max_iters;
-    const int n_uni = W.nlim + 3 * nc;  // limit and contact rows: what the adaptive penalty acts on
     if (i < m) vrinv[i] = 1.f / vrho[i];  // rho is fixed for the solve: divide once
     if (factor_fail) {
         status = KAMX_WORLD_FACTOR_FAIL;
@@ -1592,353 +2205,22 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
         if (wmode == KAMX_WARM_COLD && i < m) {
             vx[i] = vyh[i] = vzh[i] = vyp[i] = vzp[i] = vdx[i] = 0.f;
         }
-        bool converged = false;
-        float s_own = 0.f;
-        // gather balance for the loop: bodies with more than half the longest
-        // incidence list go first and take four threads per component, as
-        // far as 12 (nb + nh) <= T allows for the bucket's default workgroup
-        // size T (the same bodies, so the same sums, at every size: a
-        // four-thread body adds its rows in another order than a two-thread
-        // one); the order is bytes in the aux
-        // field (free inside the loop). Wave 0 builds it, lane b for body b
-        // (nb <= 64): a wave max, then ranks from ballots.
-        static_assert(kMaxBodies <= 64 && kMaxBodies + 1 <= 4 * MC, "gather order: one lane per body, bytes in aux");
-        unsigned char *gorder = reinterpret_cast<unsigned char *>(vaux);
-        if (tid < 64) {
-            const int kb = tid < nb ? L.inc_off[tid + 1] - L.inc_off[tid] : 0;
-            int kmax = kb;
-            for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
-            const unsigned long long below = (1ull << tid) - 1ull;
-            const unsigned long long hv = __ballot(tid < nb && 2 * kb > kmax);
-            constexpr int kGatherThreads = default_bucket_threads(MC);
-            static_assert(kGatherThreads >= 64, "gather cap from the bucket's default size");
-            const int cap = max(kGatherThreads / 12 - nb, 0);
-            const bool heavy = ((hv >> tid) & 1ull) && __popcll(hv & below) < cap;
-            const unsigned long long hm = __ballot(heavy);
-            const int nh = __popcll(hm);
-            if (tid < nb)
-                gorder[1 + (heavy ? __popcll(hm & below) : nh + tid - __popcll(hm & below))] = (unsigned char)tid;
-            if (tid == 0) gorder[0] = (unsigned char)nh;
-        }
-        __syncthreads();
-        const int gnh = gorder[0];
-        uint64_t sub[6] = {0, 0, 0, 0, 0, 0}, tmark = 0;
-        const bool timing = a.phase_clk && tid == 0;
-#define KAMX_MARK(k)                                  \
-    if (timing) {                                     \
-        uint64_t now_ = wall_clock64();               \
-        if ((k) > 0) sub[(k) > 0 ? (k) - 1 : 0] += now_ - tmark; \
-        tmark = now_;                                 \
-    }
-        // steps 4-5: rhs = -v~_f - Gamma(z^) + eta x + rho y^ + z^, and its
-        // residual against the current x (rows of this thread's block; the
-        // owner computes it for the next iteration at the end of the update)
-        auto own_rhs = [&]() {
-            if (owner_o) {
-                s_own = kind_o == kRowNormal ? mu_o * hw_sqrt(vzh[io + 1] * vzh[io + 1] + vzh[io + 2] * vzh[io + 2]) : 0.f;
-                _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                    float rr = e == 0 ? rho_o : vrho[io + e];
-                    float xe = vx[io + e];
-                    float rhs = -vvt[io + e] - (e == 0 ? s_own : 0.f) + eta * xe + rr * vyh[io + e] + vzh[io + e];
-                    vrhs[io + e] = rhs - (vdx[io + e] + (eta + rr) * xe);
-                }
-            }
-        };
-        own_rhs();
         // the solve runs in passes: a pass ends when the solve exits or when
         // the adaptive penalty changes rho, whose refactorization then runs
-        // outside the iteration loop (so the loop itself carries no calls)
-        int adapt_pending = 0;
-        it = 1;
+        // outside the iteration loop
+        int it_next = 1;
+        __syncthreads();
         for (;;) {
-            for (; it <= N; ++it) {
-                KAMX_MARK(0);
-                __syncthreads();
-                KAMX_MARK(1);
-                // t = X r over groups of 4 rows: groups g and Q-1-g form a pair
-                // (balanced: together they span Q+1 column quads); 16 threads per
-                // pair take every 16th column quad, reading the quad of r once
-                // for the 4 rows of a group. The rows of a group lie back to back,
-                // 4(G+1) floats apart; the pads of the diagonal quad hold 0 and r
-                // is 0 past row m, and rows past m (up to the next multiple of 16)
-                // hold finite values whose sums are not stored. The eight sums
-                // are reduce-scattered over the 16 lanes as in the x update.
-                {
-                    const int Q = (m + 3) >> 2;
-                    const int g = tid >> 4, kq = tid & 15;
-                    const int g1 = g, g2 = Q - 1 - g;
-                    float4 s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1;
-                    if (g1 <= g2) {
-#pragma unroll
-                        for (int part = 0; part < 2; ++part) {
-                            if (part == 1 && g2 == g1) break;
-                            const int G = part == 0 ? g1 : g2;
-                            const float *R = A + tri_row_offset(4 * G);
-                            const int rl = 4 * (G + 1);
-                            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                            for (int c = kq; c <= G; c += 16) {
-                                const float4 rv = *reinterpret_cast<const float4 *>(vrhs + 4 * c);
-                                const float4 x0 = *reinterpret_cast<const float4 *>(R + 4 * c);
-                                const float4 x1 = *reinterpret_cast<const float4 *>(R + rl + 4 * c);
-                                const float4 x2 = *reinterpret_cast<const float4 *>(R + 2 * rl + 4 * c);
-                                const float4 x3 = *reinterpret_cast<const float4 *>(R + 3 * rl + 4 * c);
-                                acc.x += x0.x * rv.x;
-                                acc.y += x1.x * rv.x;
-                                acc.z += x2.x * rv.x;
-                                acc.w += x3.x * rv.x;
-                                acc.x += x0.y * rv.y;
-                                acc.y += x1.y * rv.y;
-                                acc.z += x2.y * rv.y;
-                                acc.w += x3.y * rv.y;
-                                acc.x += x0.z * rv.z;
-                                acc.y += x1.z * rv.z;
-                                acc.z += x2.z * rv.z;
-                                acc.w += x3.z * rv.z;
-                                acc.x += x0.w * rv.w;
-                                acc.y += x1.w * rv.w;
-                                acc.z += x2.w * rv.w;
-                                acc.w += x3.w * rv.w;
-                            }
-                            if (part == 0) s1 = acc;
-                            else s2 = acc;
-                        }
-                    }
-                    const bool b3 = kq & 8, b2 = kq & 4, b1 = kq & 2;
-                    const float v8[8] = {s1.x, s1.y, s1.z, s1.w, s2.x, s2.y, s2.z, s2.w};
-                    float u4[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        u4[k] = (b3 ? v8[k + 4] : v8[k]) + dpp<kDppMirror16>(b3 ? v8[k] : v8[k + 4]);
-                    float u2[2];
-#pragma unroll
-                    for (int k = 0; k < 2; ++k)
-                        u2[k] = (b2 ? u4[k + 2] : u4[k]) + dpp<kDppMirror8>(b2 ? u4[k] : u4[k + 2]);
-                    float z = (b1 ? u2[1] : u2[0]) + dpp<kDppXor2>(b1 ? u2[0] : u2[1]);
-                    z += dpp<kDppXor1>(z);
-                    if (!(kq & 1) && g1 <= g2) {
-                        const int i = 4 * (b3 ? g2 : g1) + (b2 ? 2 : 0) + (b1 ? 1 : 0);
-                        if (i < m && (!b3 || g2 > g1)) vt[i] = z;
-                    }
-                }
-                __syncthreads();
-                KAMX_MARK(2);
-                // x_new = x + X^T t over column quads: quads c and Q-1-c form a
-                // pair (balanced: together they span m + 4 rows); 16 threads per
-                // pair take every 16th group of 4 rows, each reading a group's t
-                // and the 4 rows' entries of the quad as float4s; butterfly sum
-                // over the 16 threads
-                {
-                    const int Q = (m + 3) >> 2;
-                    const int g = tid >> 4, kq = tid & 15;
-                    const int c1 = g, c2 = Q - 1 - g;
-                    float4 s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1;
-                    if (c1 <= c2) {
-#pragma unroll
-                        for (int part = 0; part < 2; ++part) {
-                            if (part == 1 && c2 == c1) break;
-                            const int c = part == 0 ? c1 : c2;
-                            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), acc2 = acc;
-                            // four consecutive rows per step (one float4 of t), every
-                            // 64th row group; packed rows are padded to 4 floats and
-                            // the pads hold 0, so the quad that contains the diagonal
-                            // reads as-is, and t is 0 past row m (the rows there, up
-                            // to the next multiple of 4, hold finite values)
-                            for (int r = 4 * c + 4 * kq; r < m; r += 64) {
-                                const float4 tv = *reinterpret_cast<const float4 *>(vt + r);
-                                const float4 x0 = *reinterpret_cast<const float4 *>(A + tri_row_offset(r) + 4 * c);
-                                const float4 x1 = *reinterpret_cast<const float4 *>(A + tri_row_offset(r + 1) + 4 * c);
-                                const float4 x2 = *reinterpret_cast<const float4 *>(A + tri_row_offset(r + 2) + 4 * c);
-                                const float4 x3 = *reinterpret_cast<const float4 *>(A + tri_row_offset(r + 3) + 4 * c);
-                                acc.x += x0.x * tv.x;
-                                acc.y += x0.y * tv.x;
-                                acc.z += x0.z * tv.x;
-                                acc.w += x0.w * tv.x;
-                                acc2.x += x1.x * tv.y;
-                                acc2.y += x1.y * tv.y;
-                                acc2.z += x1.z * tv.y;
-                                acc2.w += x1.w * tv.y;
-                                acc.x += x2.x * tv.z;
-                                acc.y += x2.y * tv.z;
-                                acc.z += x2.z * tv.z;
-                                acc.w += x2.w * tv.z;
-                                acc2.x += x3.x * tv.w;
-                                acc2.y += x3.y * tv.w;
-                                acc2.z += x3.z * tv.w;
-                                acc2.w += x3.w * tv.w;
-                            }
-                            acc.x += acc2.x;
-                            acc.y += acc2.y;
-                            acc.z += acc2.z;
-                            acc.w += acc2.w;
-                            if (part == 0) s1 = acc;
-                            else s2 = acc;
-                        }
-                    }
-                    // reduce-scatter over the 16 lanes: halve the eight sums at each
-                    // exchange (row mirror, half-row mirror, then pairs), so that
-                    // lanes 2k and 2k+1 end with sum 4 b3 + 2 b2 + b1 of the bits
-                    // of k; the even lane writes it
-                    const bool b3 = kq & 8, b2 = kq & 4, b1 = kq & 2;
-                    const float v8[8] = {s1.x, s1.y, s1.z, s1.w, s2.x, s2.y, s2.z, s2.w};
-                    float u4[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        u4[k] = (b3 ? v8[k + 4] : v8[k]) + dpp<kDppMirror16>(b3 ? v8[k] : v8[k + 4]);
-                    float u2[2];
-#pragma unroll
-                    for (int k = 0; k < 2; ++k)
-                        u2[k] = (b2 ? u4[k + 2] : u4[k]) + dpp<kDppMirror8>(b2 ? u4[k] : u4[k + 2]);
-                    float z = (b1 ? u2[1] : u2[0]) + dpp<kDppXor2>(b1 ? u2[0] : u2[1]);
-                    z += dpp<kDppXor1>(z);
-                    if (!(kq & 1) && c1 <= c2) {
-                        const int idx = (b3 ? 4 : 0) + (b2 ? 2 : 0) + (b1 ? 1 : 0);
-                        const int j = 4 * (b3 ? c2 : c1) + (idx & 3);
-                        if (j < m && (!b3 || c2 > c1)) vxn[j] = vx[j] + z;
-                    }
-                }
-                __syncthreads();
-                KAMX_MARK(3);
-                // v~ - v~_f = D~ x_new (matrix-free, FP64): bodies gather here,
-                // each block owner evaluates its own rows below
-                delassus_gather_bal<NT>(L, nb, gnh, gorder, vp, vxn);
-                KAMX_MARK(4);
-                // steps 6-7 and the residuals of step 9 (block owners)
-                float lrp = 0.f, lrd = 0.f, lrc = 0.f, lcc = 0.f;
-                float yb[3], zb[3], xn[3], rr[3];
-                // v~ - v~_f of row io in FP64: J_a M_a^-1 g_a on the even lane,
-                // J_b M_b^-1 g_b on the odd lane, added by the pair sum
-                {
-                    double side = 0.0;
-                    if (io < m) {
-                        const int sb = hh == 0 ? L.ri(RIA, io) : L.ri(RIB, io);
-                        if (sb >= 0) {
-                            double wv[6];
-                            body_minv64(L, sb, wv);
-                            for (int c = 0; c < 6; ++c) side += (double)L.rf(RJ + 6 * hh + c, io) * wv[c];
-                        }
-                    }
-                    side = lane_group_sum<2>(side);
-                    if (hh == 0 && io < m) {
-                        const double pr = (double)vp[io];
-                        vdx[io] = (float)((side + (double)L.rf(RREG, io) * pr * (double)vxn[io]) * pr);
-                    }
-                }
-                __syncthreads();
-                if (owner_o) {
-                    float zh[3], yh[3], ri[3], vv[3];
-                    _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                        const float dx = vdx[io + e];
-                        xn[e] = vxn[io + e];
-                        zh[e] = vzh[io + e];
-                        yh[e] = vyh[io + e];
-                        rr[e] = e == 0 ? rho_o : vrho[io + e];
-                        ri[e] = vrinv[io + e];
-                        vv[e] = dx + vvt[io + e];
-                    }
-                    if (kind_o == kRowNormal) {
-                        proj_cone(mu_o, xn[0] - zh[0] * ri[0], xn[1] - zh[1] * ri[1], xn[2] - zh[2] * ri[2], yb[0], yb[1],
-                                  yb[2]);
-                    } else if (kind_o == kRowLimit) {
-                        yb[0] = fmaxf(xn[0] - zh[0] * ri[0], 0.f);
-                    } else {
-                        yb[0] = xn[0] - zh[0] * ri[0];
-                    }
-                    _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                        zb[e] = zh[e] - rr[e] * (xn[e] - yb[e]);
-                        lrp = fmaxf(lrp, fabsf(xn[e] - yb[e]));
-                        float dy = yb[e] - yh[e], dz = zb[e] - zh[e];
-                        lcc += rr[e] * dy * dy + dz * dz * ri[e];
-                    }
-                    float g = kind_o == kRowNormal ? mu_o * hw_sqrt(vv[1] * vv[1] + vv[2] * vv[2]) : 0.f;
-                    _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                        float d = vv[e] + (e == 0 ? g : 0.f) - zb[e];
-                        lrd = fmaxf(lrd, fabsf(d));
-                        if (d != d) lrd = d;
-                    }
-                    if (kind_o == kRowNormal) lrc = fabsf(yb[0] * (vv[0] + g) + yb[1] * vv[1] + yb[2] * vv[2]);
-                    else if (kind_o == kRowLimit) lrc = fabsf(yb[0] * vv[0]);
-                    if (lrp != lrp || lcc != lcc) lrp = NAN;
-                }
-                reduce4<NT>(lrp, lrd, lrc, lcc, L.red);
-                rp = lrp;
-                rd = lrd;
-                rc = lrc;
-                KAMX_MARK(5);
-                // step 8: Nesterov with adaptive restart
-                int restart = 0;
-                float beta = 0.f;
-                if (P.accel) {
-                    restart = !(lcc < P.restart_factor * c_prev);
-                    if (!restart) {
-                        float a_next = 0.5f * (1.f + hw_sqrt(1.f + 4.f * a_k * a_k));
-                        beta = (a_k - 1.f) * hw_rcp(a_next);
-                        a_k = a_next;
-                        c_prev = lcc;
-                    } else {
-                        a_k = 1.f;
-                        c_prev = c_prev / P.restart_factor;
-                    }
-                }
-                if (owner_o) {
-                    float yn[3] = {0.f, 0.f, 0.f}, zn[3] = {0.f, 0.f, 0.f};
-                    _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                        float yo = vyp[io + e], zo = vzp[io + e];
-                        if (!P.accel) {
-                            yn[e] = yb[e];
-                            zn[e] = zb[e];
-                        } else if (!restart) {
-                            yn[e] = yb[e] + beta * (yb[e] - yo);
-                            zn[e] = zb[e] + beta * (zb[e] - zo);
-                        } else {
-                            yn[e] = yo;
-                            zn[e] = zo;
-                        }
-                        vyh[io + e] = yn[e];
-                        vzh[io + e] = zn[e];
-                        vx[io + e] = xn[e];
-                        vyp[io + e] = yb[e];
-                        vzp[io + e] = zb[e];
-                    }
-                    // the next right-hand side (as own_rhs) from the values in registers
-                    s_own = kind_o == kRowNormal ? mu_o * hw_sqrt(zn[1] * zn[1] + zn[2] * zn[2]) : 0.f;
-                    _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                        float rhs = -vvt[io + e] - (e == 0 ? s_own : 0.f) + eta * xn[e] + rr[e] * yn[e] + zn[e];
-                        vrhs[io + e] = rhs - (vdx[io + e] + (eta + rr[e]) * xn[e]);
-                    }
-                }
-                KAMX_MARK(6);
-                // adaptive penalty (not in the paper: residual balancing) at the
-                // checkpoints of a solve that does not exit here; rp and rd are
-                // the same in every thread, so the branch is uniform
-                int adapt_dir = 0;
-                if (P.adapt_ratio > 0.f && n_uni > 0 && adapt_checkpoint(it, P.adapt_first) &&
-                    !(P.fixed_iters <= 0 && rp < P.eps && rd < P.eps && rc < P.eps)) {
-                    if (rd > P.adapt_ratio * rp) adapt_dir = 1;
-                    else if (rp > P.adapt_ratio * rd) adapt_dir = 2;
-                }
-                if (tid == 0 && a.rlog && P.log_restarts && it <= P.max_iters)
-                    a.rlog[(size_t)w * P.max_iters + (it - 1)] = (uint8_t)(restart | (adapt_dir << 1));
-                if (!(isfinite(rp) && isfinite(rd) && isfinite(rc))) {
-                    status = KAMX_WORLD_NONFINITE;
-                    break;
-                }
-                if (P.fixed_iters <= 0 && rp < P.eps && rd < P.eps && rc < P.eps) {
-                    converged = true;
-                    break;
-                }
-                if (adapt_dir) {
-                    adapt_pending = adapt_dir;
-                    ++it;
-                    break;
-                }
-            }
+            const int adapt_pending =
+                solve_pass<MC, NT>(args, w, m, nb, nc, row_c0, W.nlim, it_next);
+            it_next = uniform(s_int[4]);
             if (!adapt_pending) break;
             {
                 // the limit and contact rows' penalty changes by the factor;
                 // D~ + diag(eta + rho) is rebuilt, refactored and inverted, and
-                // the acceleration restarts at the current (y, z)
+                // the acceleration restarts at the current (y, z), which the
+                // owners have written as the extrapolated iterates
                 const float f = adapt_pending == 1 ? 1.f / P.adapt_factor : P.adapt_factor;
-                adapt_pending = 0;
                 __syncthreads();
                 for (int r = tid; r < m; r += NT)
                     if (L.ri(RKIND, r) != kRowBilateral) {
@@ -1946,29 +2228,19 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
                         vrinv[r] = 1.f / vrho[r];
                     }
                 __syncthreads();
-                reassemble<MC, NT>(L, A, m, nb, vp, vrho, eta);
-                if (factor_invert_again<MC, NT>(L, A, m, s_int, a, w)) {
+                reassemble<MC, NT>(m, nb, eta);
+                if (factor_invert_again<MC, NT>(m)) {
                     status = KAMX_WORLD_FACTOR_FAIL;
                     break;
                 }
-                rho_o = io < m ? vrho[io] : 1.f;
-                a_k = 1.f;
-                c_prev = INFINITY;
-                if (owner_o) {
-                    _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
-                        vyh[io + e] = vyp[io + e];
-                        vzh[io + e] = vzp[io + e];
-                    }
-                }
-                __syncthreads();
-                own_rhs();
             }
         }
-#undef KAMX_MARK
-#ifndef KAMX_FACTOR_TIMING
-        if (timing)
-            for (int k = 0; k < 6; ++k) a.phase_clk[16 * w + 8 + k] = sub[k];
-#endif
+        it = it_next;
+        status |= uniform(s_int[5]) & ~kSolveConverged;
+        const bool converged = uniform(s_int[5]) & kSolveConverged;
+        rp = __int_as_float(uniform(s_int[6]));
+        rd = __int_as_float(uniform(s_int[7]));
+        rc = __int_as_float(uniform(s_int[8]));
         if (it > N) it = N;
         if (P.fixed_iters <= 0 && !converged && status == 0) status = KAMX_WORLD_MAXITER;
         __syncthreads();
@@ -2086,15 +2358,10 @@ __device__ __attribute__((noinline)) void step_world(const StepArgs &a, int k, i
 // unit for another world's workgroup.
 template <int MC, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel(StepArgs a) {
-    __shared__ int s_int[8];
-    // the arguments in LDS: the per-step function takes them by reference,
-    // which would otherwise copy them to every lane's private stack
-    __shared__ StepArgs sa;
-    if (threadIdx.x == 0) sa = a;
-    __syncthreads();
+    KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
 #pragma clang loop unroll(disable)
-    for (int k = 0; k < sa.nsteps; ++k) {
-        step_world<MC, NT>(sa, k, s_int);
+    for (int k = 0; k < a.nsteps; ++k) {
+        step_world<MC, NT>(args, k);
         __syncthreads();
     }
 }
