@@ -94,6 +94,18 @@ __device__ inline double dpp(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Lane N of every row of 16 lanes, in all lanes of the row.
+template <int N>
+__device__ inline float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xF, 0xF, true));
+}
+
+// A constant as an argument, for what must be known at compile time.
+template <int V>
+struct Const {
+    static constexpr int value = V;
+};
+
 // A row's last lane broadcast to the next row (kDppBcast15), the second row's to
 // the third and fourth (kDppBcast31); rows outside ROWS get +0.
 enum { kDppBcast15 = 0x142, kDppBcast31 = 0x143 };

@@ -185,8 +185,9 @@ struct StepArgs {
 
 // Packed lower-triangular storage with every row padded to a multiple of 4
 // floats (so rows can be read as float4): offset of row i.
+// (i < 256; the masks tell the compiler that a 24-bit multiply will do)
 __host__ __device__ inline int tri_row_offset(int i) {
-    int a = i >> 2, b = i & 3;
+    const int a = (i >> 2) & 63, b = i & 3;
     return 4 * (a + 1) * (2 * a + b);
 }
 
