@@ -156,4 +156,14 @@ __device__ inline float rdlane(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// A value every lane holds, as a scalar.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// a + b rounded by itself (never fused with a product that forms a or b)
+__device__ inline float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
+__device__ inline float uniform(float v) { return __int_as_float(uniform(__float_as_int(v))); }
+
 }  // namespace kamx

@@ -1,4 +1,5 @@
-"""The dense solve at the sizes where its tiling changes: one step of worlds
+"""The dense solve at the sizes where its tiling changes: one step (and forward
+kinematics, which shares the factorization) of worlds
 whose row counts sit at the edges of 4-row quads, 16-row tiles and size
 buckets, against the oracle with the GPU's restart decisions replayed.  The
 bar is the parity tests' 1e-4 relative per world on u+ and the net impulses per
@@ -13,6 +14,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
+import oracle  # noqa: E402
 from paper_2603_16536_amd import kamx, scenes  # noqa: E402
 
 from parity_util import compare_worlds, gpu_step, summary  # noqa: E402
@@ -48,3 +50,29 @@ def test_contact_rows_on_one_body(points):
     rng = np.random.default_rng(200 + points)
     one = [scenes.box_point_contacts(rng, points, mu=0.5, gap_scale=1e-3) for _ in range(3)]
     check(scenes.round_to_f32(scenes.concat(one)), [3 * points] * 3, f"{points} contacts")
+
+
+@pytest.mark.parametrize("joints", [1, 2, 3, 8, 11, 16, 21, 24, 32, 37])
+def test_kinematics_at_tile_edges(joints):
+    """Chains with every joint targeted (6 to 222 rows).  The iteration stops at
+    |F| <= 3e-7 in FP64; the poses it returns are rounded to FP32, half an ulp
+    of the largest coordinate R per component and of 1 per quaternion entry, and a
+    constraint sees four such roundings over levers of at most R."""
+    tol = 3e-7
+    rng = np.random.default_rng(300 + joints)
+    one = [scenes.random_chain_world(rng, joints, with_limits=False, on_manifold=True) for _ in range(3)]
+    scene = scenes.round_to_f32(scenes.concat(one))
+    targets = rng.uniform(-0.2, 0.2, scene.n_joints).astype(np.float32)
+    m = kamx.Model(scene)
+    it, res = m.forward_kinematics(targets, max_iters=50, tol=tol)
+    q = m.state()[0].cpu().numpy().astype(np.float64)
+    it, res = it.cpu().numpy(), res.cpu().numpy()
+    m.close()
+    assert np.all(res <= tol) and np.all(it < 50)
+    sg = scene.replace(q=q)
+    R = np.abs(q[:, :3]).max()
+    bound = tol + 4 * 2.0 ** -24 * (R + 2.0 * max(R, 1.0))
+    f = max(np.abs(oracle.world_system(sg, oracle.Params(dt=scene.dt), w)["f"]).max() for w in range(3))
+    c = max(abs(oracle.joint_coordinate(sg, q, j)[0] - targets[j]) for j in range(scene.n_joints))
+    print(f"\n{joints} joints: {it.max()} iterations, constraints {f:.1e}, targets {c:.1e} (bound {bound:.1e})", flush=True)
+    assert f < bound and c < bound
