@@ -8,6 +8,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "kamx_internal.h"
+
 namespace kamx {
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).
@@ -165,5 +167,26 @@ __device__ inline float add_rounded(float a, float b) {
 }
 
 __device__ inline float uniform(float v) { return __int_as_float(uniform(__float_as_int(v))); }
+
+// The launch arguments where the kernel received them: read by scalar loads,
+// they and what follows from them (sizes, branches) are uniform to the compiler
+// and stay out of the vector registers.
+typedef const __attribute__((address_space(4))) StepArgs KernelArgs;
+typedef const __attribute__((address_space(4))) SolverParams SolverArgs;
+
+__device__ inline KernelArgs *uniform_args(KernelArgs *a) {
+    const uint64_t v = (uint64_t)a;
+    return (KernelArgs *)(((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v));
+}
+
+// A world's record as scalars.
+__device__ inline WorldInfo uniform_world(const WorldInfo *w) {
+    WorldInfo W;
+    const int32_t *src = reinterpret_cast<const int32_t *>(w);
+    int32_t *dst = reinterpret_cast<int32_t *>(&W);
+#pragma unroll
+    for (int e = 0; e < (int)(sizeof(WorldInfo) / 4); ++e) dst[e] = uniform(src[e]);
+    return W;
+}
 
 }  // namespace kamx

@@ -26,7 +26,7 @@
 // by DPP quad permutations, with no LDS traffic and no owner thread.
 #include <math.h>
 
-#include "kamx_device.h"
+#include "kamx_factor.h"
 #include "kamx_geom.h"
 #include "kamx_internal.h"
 
@@ -47,28 +47,48 @@ enum { SRBIAS = 0, SRMU = 1, SRREG = 2, SRKIND = 3 };
 
 constexpr int kRowPad = -1;  // an inactive row (alignment padding, or past the world's rows)
 
+// Rows of a gather task (body, component) held in registers through the solve; the
+// rest of a longer list goes through LDS.
+constexpr int kSpGatherRegs = 10;
+
+// The rows of body b's list that its tasks' threads hold: none where a task has no
+// thread of its own.
+__host__ __device__ constexpr int sp_held_rows(int nt, int b) { return 6 * b + 5 < nt ? kSpGatherRegs : 0; }
+
+// The products of a Delassus application that go through LDS, [row side][6] doubles,
+// share it with what a solve no longer reads: joint fields, raw rows, row data.
+// Sixteen entries past the last are read and not used.
+__host__ __device__ constexpr int sp_product_floats(int nt) {
+    const int products = 2 * 6 * 2 * nt, rows = 16 * kSpJoints + 21 * nt;
+    return (products > rows ? products : rows) + 16 * 12;
+}
+
 // LDS footprint in floats for a workgroup of NT threads (doubles first)
 __host__ __device__ constexpr int sp_smem_floats(int nt) {
     return 2 * 7 * kSpBodies + 2 * 6 * kSpBodies        // FP64 poses, FP64 gather sums
-           + 32 * kSpBodies + 16 * kSpJoints + 12 * kMaxContacts
-           + 12 * nt + 4 * nt + nt + nt                // J~, row scratch, row bodies, vector
-           + (((kSpBodies + 1 + 2 * nt) + 3) & ~3)    // incidence lists
-           + 128;                                      // reduction partials (two buffers)
+           + 32 * kSpBodies + 12 * kMaxContacts
+           + nt + 4 + 2 * ((kSpBodies + 1 + 3) & ~3)   // vector, incidence offsets
+           + 512 + 16                                  // reduction partials (two buffers), hand-over ints
+           + sp_product_floats(nt);
 }
 
 struct SpLds {
     double *qd;   // [7][kSpBodies] poses the rows are built at (FP64)
-    double *g;    // [6][kSpBodies] body gather sums of the last product (FP64)
+    double *g;    // [kSpBodies][6] body gather sums of the last product (FP64)
     float *b;     // [32][kSpBodies]
     float *j;     // [16][kSpJoints]
     float *c;     // [12][kMaxContacts]
     float *J;     // [12][nt] raw rows, then J~
     float *rs;    // [4][nt] row scratch
     int *rab;     // [nt] (a + 1) | (b + 1) << 16, 0: none
-    float *v;     // [nt] the vector of the current product
+    float *v;     // [nt + 4] the vector of the current product, then zeros
     int *inc_off;   // [kSpBodies + 1]
+    int *rest_off;  // [kSpBodies + 1] the same for the entries past sp_held_rows
     int *inc_list;  // [2 nt] (row << 1) | side
-    float *red;   // [2][16 waves][4]
+    int *inc_pos;   // [nt][2] a row side's place in its body's list
+    double *prod;   // [2 nt][6] J~^T v of the entries past sp_held_rows (over j .. inc_pos)
+    float *red;   // [2][256] partial results of the reductions
+    int *s_int;   // [16] values one thread hands to all
     int nt;
     __device__ float &bf(int f, int i) const { return b[f * kSpBodies + i]; }
     __device__ float &jfld(int f, int i) const { return j[f * kSpJoints + i]; }
@@ -79,6 +99,35 @@ struct SpLds {
     __device__ int &ri(int f, int r) const { return reinterpret_cast<int *>(rs)[f * nt + r]; }
 };
 
+template <int NT>
+__device__ inline SpLds sp_views() {
+    extern __shared__ float4 smem4[];
+    // the base as an opaque number: a function other than the kernel would load it
+    // from memory again in front of every product
+    unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) char *)(char *)smem4;
+    asm volatile("" : "+s"(base));
+    float *sm = (float *)(__attribute__((address_space(3))) float *)(size_t)base;
+    SpLds L;
+    L.nt = NT;
+    L.qd = reinterpret_cast<double *>(sm);
+    L.g = L.qd + 7 * kSpBodies;
+    L.b = reinterpret_cast<float *>(L.g + 6 * kSpBodies);
+    L.c = L.b + 32 * kSpBodies;
+    L.inc_off = reinterpret_cast<int *>(L.c + 12 * kMaxContacts);
+    L.rest_off = L.inc_off + ((kSpBodies + 1 + 3) & ~3);
+    L.v = reinterpret_cast<float *>(L.rest_off + ((kSpBodies + 1 + 3) & ~3));
+    L.red = L.v + NT + 4;
+    L.s_int = reinterpret_cast<int *>(L.red + 512);
+    L.j = reinterpret_cast<float *>(L.s_int + 16);
+    L.prod = reinterpret_cast<double *>(L.j);
+    L.J = L.j + 16 * kSpJoints;
+    L.rs = L.J + 12 * NT;
+    L.rab = reinterpret_cast<int *>(L.rs + 4 * NT);
+    L.inc_list = L.rab + NT;
+    L.inc_pos = L.inc_list + 2 * NT;
+    return L;
+}
+
 // Broadcast of quad lane K to the four lanes of its aligned quad (DPP quad
 // permutation); every lane of the wave must be active.
 template <int K>
@@ -86,60 +135,82 @@ __device__ inline float quad_bc(float v) {
     return dpp<K * 0x55>(v);
 }
 
-// Sums over the workgroup of up to four per-thread values (fixed order: DPP
-// rows of 16, readlane across the wave, waves in index order through LDS;
-// every thread ends with the same bits).  buf alternates between two
-// halves of red, so consecutive reductions need one barrier each.
+// The NW waves' partial results v (lane q of every row of 16 lanes holds wave
+// q's) added in wave order.
+template <int NW, int Q = 1>
+__device__ inline float sum_in_order(float v, float acc) {
+    if constexpr (Q < NW) return sum_in_order<NW, Q + 1>(v, acc + row_bcast<Q>(v));
+    return acc;
+}
+
+// Lanes of the quads QUADS of every row of 16 take the lane CTRL (a quad
+// permutation) names, the others keep theirs.
+template <int CTRL, int QUADS>
+__device__ inline float quads_from(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xF, QUADS, false));
+}
+
+// Sums over the workgroup of the products f[k] g[k] (fixed order: DPP rows of 16,
+// the wave's rows as (row 3 + row 2) + (row 1 + row 0), waves in index order; every
+// thread ends with the same bits).  A reduction is issue time of all 16 waves, so
+// the values share it: from the quads on, lane k of a quad carries value k, a row's
+// result goes to LDS at once, and the last sums run on lane 16 k + w for value k
+// of wave w.  buf alternates between two halves of red, so consecutive reductions
+// need one barrier each.
 template <int NT, int NV>
-__device__ inline void sp_sum(float (&s)[4], float *red, int &buf) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float *rb = red + 64 * buf;
+__device__ inline void sp_sum(const float (&f)[3], const float (&g)[3], float (&s)[3], float *red, int &buf) {
+    constexpr int NW = NT / 64;
+    static_assert(NV >= 2 && NV <= 3 && NW <= 16, "a lane of a quad per value, a lane of a row per wave");
+    const int lane = threadIdx.x & 63;
+    float *rb = red + 256 * buf;
+    float v[3];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        float v = lane_group_sum<16>(s[k]);
-        v = (rdlane(v, 0) + rdlane(v, 16)) + (rdlane(v, 32) + rdlane(v, 48));
-        if (lane == 0) rb[4 * wave + k] = v;
+    for (int k = 0; k < NV; ++k) v[k] = __builtin_fmaf(f[k], g[k], dpp<kDppXor1>(f[k] * g[k]));
+    // (of a pair, quads 0 and 2 of a row take the even lane's, quads 1 and 3 the odd lane's)
+    v[0] = quads_from<0xF5, 0xa>(v[0]);
+    v[1] = quads_from<0xA0, 0x5>(v[1]);
+    float t = lane & 1 ? v[1] : v[0];
+    t += dpp<kDppXor2>(t);
+    if constexpr (NV == 3) {
+        v[2] = quads_from<0xF5, 0xa>(v[2]);
+        v[2] += dpp<kDppXor2>(v[2]);
+        t = lane & 2 ? v[2] : t;
     }
+    t += dpp<0x104>(t);  // lane + 4: quads 0 and 2 of a row
+    t += dpp<0x108>(t);  // lane + 8: quad 0
+    if ((lane & 15) < NV) rb[4 * (16 * (lane & 15) + (threadIdx.x >> 6)) + (lane >> 4)] = t;
     __syncthreads();
+    const mfx4 part = *reinterpret_cast<const mfx4 *>(rb + 4 * ((lane & 48) | (lane & (NW - 1))));
+    const float w = (part[3] + part[2]) + (part[1] + part[0]);
+    const float sum = sum_in_order<NW>(w, row_bcast<0>(w));
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        float acc = rb[k];
-        for (int q = 1; q < NT / 64; ++q) acc += rb[4 * q + k];
-        s[k] = acc;
-    }
+    for (int k = 0; k < NV; ++k)
+        s[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 16 * k));
     buf ^= 1;
 }
 
 // Maxima (m0..m2, values >= +0 or NaN) and one sum (s3) over the workgroup.
 template <int NT>
 __device__ inline void sp_max3_sum(float &m0, float &m1, float &m2, float &s3, float *red, int &buf) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float *rb = red + 64 * buf;
-    m0 = lane_group_max<16>(m0);
-    m1 = lane_group_max<16>(m1);
-    m2 = lane_group_max<16>(m2);
+    constexpr int NW = NT / 64;
+    static_assert(NW >= 4 && NW <= 16, "one lane of a row per wave");
+    float *rb = red + 256 * buf;
+    auto wave_max = [](float v) {
+        v = lane_group_max<16>(v);
+        v = max_nonneg(v, dpp_rows<kDppBcast15, 0xa>(v));
+        return max_nonneg(v, dpp_rows<kDppBcast31, 0xc>(v));
+    };
     s3 = lane_group_sum<16>(s3);
-    m0 = max_nonneg(max_nonneg(rdlane(m0, 0), rdlane(m0, 16)), max_nonneg(rdlane(m0, 32), rdlane(m0, 48)));
-    m1 = max_nonneg(max_nonneg(rdlane(m1, 0), rdlane(m1, 16)), max_nonneg(rdlane(m1, 32), rdlane(m1, 48)));
-    m2 = max_nonneg(max_nonneg(rdlane(m2, 0), rdlane(m2, 16)), max_nonneg(rdlane(m2, 32), rdlane(m2, 48)));
-    s3 = (rdlane(s3, 0) + rdlane(s3, 16)) + (rdlane(s3, 32) + rdlane(s3, 48));
-    if (lane == 0) {
-        rb[4 * wave + 0] = m0;
-        rb[4 * wave + 1] = m1;
-        rb[4 * wave + 2] = m2;
-        rb[4 * wave + 3] = s3;
-    }
+    s3 += dpp_rows<kDppBcast15, 0xa>(s3);
+    s3 += dpp_rows<kDppBcast31, 0xc>(s3);
+    mfx4 part = {wave_max(m0), wave_max(m1), wave_max(m2), s3};
+    if ((threadIdx.x & 63) == 63) *reinterpret_cast<mfx4 *>(rb + 4 * (threadIdx.x >> 6)) = part;
     __syncthreads();
-    m0 = rb[0];
-    m1 = rb[1];
-    m2 = rb[2];
-    s3 = rb[3];
-    for (int q = 1; q < NT / 64; ++q) {
-        m0 = max_nonneg(m0, rb[4 * q]);
-        m1 = max_nonneg(m1, rb[4 * q + 1]);
-        m2 = max_nonneg(m2, rb[4 * q + 2]);
-        s3 = s3 + rb[4 * q + 3];
-    }
+    part = *reinterpret_cast<const mfx4 *>(rb + 4 * (threadIdx.x & (NW - 1)));
+    m0 = uniform(lane_group_max<NW>(part[0]));
+    m1 = uniform(lane_group_max<NW>(part[1]));
+    m2 = uniform(lane_group_max<NW>(part[2]));
+    s3 = uniform(sum_in_order<NW>(part[3], row_bcast<0>(part[3])));
     buf ^= 1;
 }
 
@@ -164,34 +235,97 @@ __device__ inline void half_inv_mass(const SpLds &L, int b, const float in[6], f
     for (int k = 0; k < 3; ++k) out[3 + k] = s[k];
 }
 
+// This thread's part of the product: its first gather task with the rows it
+// holds and the rest of its list, and where its row's two 6-vectors go if they are
+// in the rest of a list (-1: not).
+struct SpGather {
+    float J[kSpGatherRegs];         // J~ of the task's first rows
+    unsigned v[kSpGatherRegs / 2];  // where in L.v their entries are, two 16-bit byte offsets
+    int k0, n;                      // the rest
+    int pa, pb;
+};
+
 // One product D~ v: thread t contributes v_t (0 on inactive rows and
 // threads); returns (D~ v)_t.  The body gather sums J~_b^T v (FP64) stay in
-// L.g until the next product.  Two barriers.
+// L.g until the next product.  Two barriers.  A task's sum over its body's rows is
+// one chain in row order.  Its thread holds the first rows' J~ and reads their v, all
+// before the first sum.  Of a longer list the rows' threads write the exact
+// products J~ v (two floats in FP64), so that the rest of the chain is one read and
+// one addition per row, the reads a fixed stride apart: two bodies of the figure
+// carry 61 rows, and with list, J~ and v behind every term their chain took 5500 of a
+// product's 9000 cycles.  All entries through LDS made a product 6500 cycles, 4700 of
+// them in the traffic.
 template <int NT>
-__device__ inline float sp_apply(const SpLds &L, const SpRow &R, int nb, float vt) {
+__device__ inline float sp_apply(const SpLds &L, const SpRow &R, const SpGather &G, int nb, float vt) {
     const int tid = threadIdx.x;
     L.v[tid] = vt;
-    __syncthreads();
-    for (int task = tid; task < 6 * nb; task += NT) {
-        const int bb = task / 6, c = task - 6 * (task / 6);
-        double acc = 0.0;
-        const int k1 = L.inc_off[bb + 1];
-        for (int k = L.inc_off[bb]; k < k1; ++k) {
-            const int e = L.inc_list[k];
-            const int r = e >> 1;
-            acc += (double)L.J[(6 * (e & 1) + c) * NT + r] * (double)L.v[r];
+    {
+        const double vd = (double)vt;
+        if (G.pa >= 0) {
+            double2 *o = reinterpret_cast<double2 *>(L.prod + 6 * G.pa);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[c] = make_double2((double)R.jt[2 * c] * vd, (double)R.jt[2 * c + 1] * vd);
         }
-        L.g[c * kSpBodies + bb] = acc;
+        if (G.pb >= 0) {
+            double2 *o = reinterpret_cast<double2 *>(L.prod + 6 * G.pb);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                o[c] = make_double2((double)R.jt[6 + 2 * c] * vd, (double)R.jt[6 + 2 * c + 1] * vd);
+        }
     }
     __syncthreads();
-    double out = 0.0;
-    if (R.kind != kRowPad) {
-        for (int c = 0; c < 6; ++c) out += (double)R.jt[c] * L.g[c * kSpBodies + R.a];
-        if (R.b >= 0)
-            for (int c = 0; c < 6; ++c) out += (double)R.jt[6 + c] * L.g[c * kSpBodies + R.b];
-        out += (double)R.preg * (double)vt;
+    // entries k0 .. k0 + n - 1 of component c: eight at a time, the next eight read
+    // before these are added
+    auto rest = [&](int k0, int n, int c, double acc) {
+        const double *p = L.prod + 6 * k0 + c;
+        double e[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) e[q] = p[6 * q];
+        for (; n > 8; n -= 8) {
+            double f[8];
+            p += 48;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) f[q] = p[6 * q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += e[q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) e[q] = f[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += q < n ? e[q] : 0.0;
+        return acc;
+    };
+    if (tid < 6 * nb) {
+        float vv[kSpGatherRegs];
+#pragma unroll
+        for (int q = 0; q < kSpGatherRegs; ++q) 
+            vv[q] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(L.v) + (q & 1 ? G.v[q / 2] >> 16 : G.v[q / 2] & 0xffff));
+        double acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < kSpGatherRegs; ++q) {
+            float Jq = G.J[q];
+            asm volatile("" : "+v"(Jq));  // (kept as a float: doubles would take another 12 registers)
+            acc += (double)Jq * (double)vv[q];
+        }
+        if (G.n > 0) acc = rest(G.k0, G.n, tid - 6 * (tid / 6), acc);
+        L.g[tid] = acc;
     }
-    return (float)out;
+    for (int task = tid + NT; task < 6 * nb; task += NT) {
+        const int bb = task / 6;
+        L.g[task] = rest(L.rest_off[bb], L.rest_off[bb + 1] - L.rest_off[bb], task - 6 * bb, 0.0);
+    }
+    __syncthreads();
+    const int ia = R.kind != kRowPad ? R.a : 0, ib = R.kind != kRowPad && R.b >= 0 ? R.b : 0;
+    double ga[6], gb[6];
+    for (int c = 0; c < 6; ++c) ga[c] = L.g[6 * ia + c];
+    for (int c = 0; c < 6; ++c) gb[c] = L.g[6 * ib + c];
+    double out = 0.0;
+    for (int c = 0; c < 6; ++c) out += (double)R.jt[c] * ga[c];
+    double both = out;
+    for (int c = 0; c < 6; ++c) both += (double)R.jt[6 + c] * gb[c];
+    out = R.b >= 0 ? both : out;
+    out += (double)R.preg * (double)vt;
+    return R.kind != kRowPad ? (float)out : 0.f;
 }
 
 // Pi_K of a row's entry of w (Alg. 1 step 6): identity on bilateral rows,
@@ -216,31 +350,257 @@ __device__ inline float sp_gamma(const SpRow &R, float mu, float w) {
     return R.kind == kRowNormal ? mu * sqrtf(w1 * w1 + w2 * w2) : 0.f;
 }
 
+// The PADMM solve of a world (Alg. 1 steps 2-10) on the rows the step built: a
+// function of its own, so that the registers of its loop are its own.  In: J~, the
+// bodies, the incidence lists and, per row, v~_f (SRBIAS), mu, p^2 R (SRREG), kind
+// and the warm start's y (L.v).  Out: x, y, z per row (SRBIAS, SRMU, SRREG), the
+// gather sums of y in L.g and, in s_int, [4] iterations, [5] status, [6..9] r_p,
+// r_d, r_c, r_ncp.
+// On the figure (151 bodies, 1014 rows on 1024 threads) a Delassus product with its
+// Conjugate Residual update takes 2.3 us (2.8 rows, reductions and scalars, 2.6 waiting
+// for the longest chain, in thousands of cycles), and a world's step 1.25 ms against
+// 5.3 ms with the row data spilled, list, J~ and v read in front of every term of every
+// chain and every thread adding up every wave's partial sums.
 template <int NT>
-__device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, int k, int *s_int) {
-    extern __shared__ float4 smem4[];
-    float *sm = reinterpret_cast<float *>(smem4);
+__device__ __attribute__((noinline)) void sp_solve(KernelArgs *args, int w, int nb, int rc0p, int n_uni, int warm) {
     const int tid = threadIdx.x;
-    const int w = a.bucket_worlds[blockIdx.x];
-    const uint32_t step = *a.step_ctr + (uint32_t)k;
-    const WorldInfo W = a.worlds[w];
-    const SolverParams &P = a.p;
-
-    SpLds L;
-    L.nt = NT;
-    L.qd = reinterpret_cast<double *>(sm);
-    L.g = L.qd + 7 * kSpBodies;
-    L.b = reinterpret_cast<float *>(L.g + 6 * kSpBodies);
-    L.j = L.b + 32 * kSpBodies;
-    L.c = L.j + 16 * kSpJoints;
-    L.J = L.c + 12 * kMaxContacts;
-    L.rs = L.J + 12 * NT;
-    L.rab = reinterpret_cast<int *>(L.rs + 4 * NT);
-    L.v = reinterpret_cast<float *>(L.rab + NT);
-    L.inc_off = reinterpret_cast<int *>(L.v + NT);
-    L.inc_list = L.inc_off + kSpBodies + 1;
-    L.red = reinterpret_cast<float *>(L.inc_off + (((kSpBodies + 1 + 2 * NT) + 3) & ~3));
+    KernelArgs &a = *uniform_args(args);
+    SolverArgs &P = a.p;
+    w = uniform(w);
+    nb = uniform(nb);
+    rc0p = uniform(rc0p);
+    n_uni = uniform(n_uni);
+    warm = uniform(warm);
+    const SpLds L = sp_views<NT>();
     int rbuf = 0;
+    SpRow R;
+    R.kind = L.ri(SRKIND, tid);
+    {
+        const int ab = L.rab[tid];
+        R.a = (ab & 0xffff) - 1;
+        R.b = (ab >> 16) - 1;
+    }
+    for (int e = 0; e < 12; ++e) R.jt[e] = L.J[e * NT + tid];
+    R.preg = L.rf(SRREG, tid);
+    const float vf = L.rf(SRBIAS, tid), mu = L.rf(SRMU, tid), ws = L.v[tid];
+    const int qe = (tid - rc0p) & 3;  // lane within a contact quad
+    SpGather G;
+    {
+        const int bb = tid / 6, c = tid - 6 * (tid / 6);
+        const bool on = tid < 6 * nb;
+        const int k0 = on ? L.inc_off[bb] : 0;
+        const int held = on ? min(L.inc_off[bb + 1] - k0, sp_held_rows(NT, bb)) : 0;
+#pragma unroll
+        for (int q = 0; q < kSpGatherRegs; ++q) {
+            const bool have = q < held;
+            const int e = have ? L.inc_list[k0 + q] : 0;
+            G.J[q] = have ? L.J[(6 * (e & 1) + c) * NT + (e >> 1)] : 0.f;
+            const unsigned o = 4 * (have ? e >> 1 : NT);
+            G.v[q / 2] = q & 1 ? G.v[q / 2] | o << 16 : o;
+        }
+        if (tid < 4) L.v[NT + tid] = 0.f;  // read in place of rows a task does not have
+        G.k0 = on ? L.rest_off[bb] : 0;
+        G.n = on ? L.rest_off[bb + 1] - G.k0 : 0;
+        auto place = [&](int b, int side) {
+            const int pos = L.inc_pos[2 * tid + side] - sp_held_rows(NT, b);
+            return pos >= 0 ? L.rest_off[b] + pos : -1;
+        };
+        G.pa = R.a >= 0 ? place(R.a, 0) : -1;
+        G.pb = R.b >= 0 && R.b != R.a ? place(R.b, 1) : -1;
+    }
+    // (rho, 1/rho and the shift change only with the adaptive penalty)
+    float rho = R.kind == kRowBilateral ? P.rho_bil : (R.kind == kRowPad ? 1.f : P.rho_c);
+    float rinv = 1.f / rho;
+    const float eta = P.eta;
+    float shift = eta + rho;  // diagonal of D~ + diag(eta + rho) beyond D~
+    const bool unilateral = R.kind == kRowLimit || R.kind == kRowNormal || R.kind == kRowTangent;
+
+    // warm start: y = x = Pi_K(lambda_ws / p), z = v~(y) + Gamma(v~(y)) on
+    // unilateral rows, 0 on bilateral rows; cold: all zero
+    float x = 0.f, y = 0.f, z = 0.f, Dx = 0.f;
+    __syncthreads();
+    if (warm) {
+        y = sp_project(R, mu, qe, ws);
+        x = y;
+        Dx = sp_apply<NT>(L, R, G, nb, y);
+        const float v0 = Dx + vf;
+        const float gm = sp_gamma(R, mu, v0);
+        z = unilateral ? v0 + gm : 0.f;
+    }
+    float yh = y, zh = z;  // extrapolated iterates
+    float yp = y, zp = z;  // iterates of the previous iteration
+
+    // ---- PADMM (Alg. 1 steps 3-10) with the x-update (step 5) by Conjugate
+    //      Residual on A = D~ + diag(eta + rho): cr_iters iterations from the
+    //      previous x (Sec. 5.1); A x of the previous iterate is known from
+    //      the residual evaluation, so the solve starts from
+    //      r0 = rhs - A x without a product.
+    float a_k = 1.f, c_prev = INFINITY;
+    int it = 0, status = 0;
+    float rp = 0.f, rd = 0.f, rc = 0.f, rncp = 0.f;
+    const int fixed_iters = P.fixed_iters, max_iters = P.max_iters, accel = P.accel;
+    const float eps = P.eps, restart_factor = P.restart_factor, adapt_ratio = P.adapt_ratio;
+    const int N = fixed_iters > 0 ? fixed_iters : max_iters;
+    // the next checkpoint of the adaptive penalty (adapt_first, then doubling; -1: none)
+    int check = adapt_ratio > 0.f && n_uni > 0 && P.adapt_first > 0 ? P.adapt_first : -1;
+    const int ncr = P.cr_iters > 0 ? P.cr_iters : 1;
+    bool converged = false;
+    for (it = 1; it <= N; ++it) {
+        // steps 4-5: s = Gamma(z^), rhs = -v~_f - s + eta x + rho y^ + z^
+        const float s = sp_gamma(R, mu, zh);
+        const float rhs = R.kind == kRowPad ? 0.f : -vf - s + eta * x + rho * yh + zh;
+        float r = rhs - (Dx + shift * x);
+        float pc = r;
+        float Ap = sp_apply<NT>(L, R, G, nb, r) + shift * r;
+        float sums[3];
+        sp_sum<NT, 2>({r, Ap, 0.f}, {Ap, Ap, 0.f}, sums, L.red, rbuf);
+        float rAr = sums[0], ApAp = sums[1];
+        for (int q = 0; q < ncr; ++q) {
+            if (!(ApAp > 0.f) || !(rAr > 0.f)) break;  // exact, or no further progress
+            const float alpha = rAr / ApAp;
+            x += alpha * pc;
+            r -= alpha * Ap;
+            if (q + 1 == ncr) break;
+            const float Ar = sp_apply<NT>(L, R, G, nb, r) + shift * r;
+            float s3[3];
+            sp_sum<NT, 3>({r, Ar, Ap}, {Ar, Ar, Ar}, s3, L.red, rbuf);
+            const float beta = s3[0] / rAr;
+            rAr = s3[0];
+            pc = r + beta * pc;
+            Ap = Ar + beta * Ap;
+            ApAp = s3[1] + 2.f * beta * s3[2] + beta * beta * ApAp;
+        }
+        // v~ - v~_f = D~ x for the dual residual and the next right-hand side
+        Dx = sp_apply<NT>(L, R, G, nb, x);
+        // steps 6-7
+        const float yb = sp_project(R, mu, qe, x - zh * rinv);
+        const float zb = zh - rho * (x - yb);
+        // step 9: residuals (preconditioned units)
+        const float vv = Dx + vf;
+        const float gm = sp_gamma(R, mu, vv);
+        float lrp = fabsf(x - yb);
+        float dres = vv + gm - zb;
+        float lrd = fabsf(dres);
+        if (dres != dres) lrd = dres;
+        // complementarity per unilateral block: y . (v~ + Gamma) over a
+        // contact's quad (every lane takes part in the quad sum), y v~ on a
+        // limit row
+        const bool cont = R.kind == kRowNormal || R.kind == kRowTangent;
+        const float qsum = lane_group_sum<4>(cont ? yb * (vv + gm) : 0.f);
+        float lrc = R.kind == kRowNormal ? fabsf(qsum) : (R.kind == kRowLimit ? fabsf(yb * vv) : 0.f);
+        const float dy = yb - yh, dz = zb - zh;
+        float lcc = R.kind == kRowPad ? 0.f : rho * dy * dy + dz * dz * rinv;
+        if (R.kind == kRowPad) lrp = lrd = 0.f;
+        if (lrp != lrp || lcc != lcc) lrp = NAN;
+        sp_max3_sum<NT>(lrp, lrd, lrc, lcc, L.red, rbuf);
+        rp = lrp;
+        rd = lrd;
+        rc = lrc;
+        // step 8: Nesterov with adaptive restart
+        int restart = 0;
+        float beta = 0.f;
+        if (accel) {
+            restart = !(lcc < restart_factor * c_prev);
+            if (!restart) {
+                const float a_next = 0.5f * (1.f + sqrtf(1.f + 4.f * a_k * a_k));
+                beta = (a_k - 1.f) / a_next;
+                a_k = a_next;
+                c_prev = lcc;
+            } else {
+                a_k = 1.f;
+                c_prev = c_prev / restart_factor;
+            }
+        }
+        if (!accel) {
+            yh = yb;
+            zh = zb;
+        } else if (!restart) {
+            yh = yb + beta * (yb - yp);
+            zh = zb + beta * (zb - zp);
+        } else {
+            yh = yp;
+            zh = zp;
+        }
+        yp = yb;
+        zp = zb;
+        // adaptive penalty (not in the paper: residual balancing) at the
+        // checkpoints of a solve that does not exit here; the residuals are
+        // the same in every thread, so the decision is uniform
+        int adapt_dir = 0;
+        if (it == check) {
+            check = check < (1 << 29) ? 2 * check : 0x7fffffff;
+            if (!(fixed_iters <= 0 && rp < eps && rd < eps && rc < eps)) {
+                if (rd > adapt_ratio * rp) adapt_dir = 1;
+                else if (rp > adapt_ratio * rd) adapt_dir = 2;
+            }
+        }
+        if (tid == 0 && a.rlog && P.log_restarts && it <= max_iters)
+            a.rlog[(size_t)w * max_iters + (it - 1)] = (uint8_t)(restart | (adapt_dir << 1));
+        if (!(isfinite(rp) && isfinite(rd) && isfinite(rc))) {
+            status = KAMX_WORLD_NONFINITE;
+            break;
+        }
+        if (fixed_iters <= 0 && rp < eps && rd < eps && rc < eps) {
+            converged = true;
+            break;
+        }
+        if (adapt_dir) {
+            // the limit and contact rows' penalty changes by the factor (the
+            // operator is applied matrix-free, so nothing is refactored) and
+            // the acceleration restarts at the current (y, z)
+            if (unilateral) {
+                rho *= adapt_dir == 1 ? 1.f / P.adapt_factor : P.adapt_factor;
+                rinv = 1.f / rho;
+                shift = eta + rho;
+            }
+            a_k = 1.f;
+            c_prev = INFINITY;
+            yh = yp;
+            zh = zp;
+        }
+    }
+    if (it > N) it = N;
+    if (fixed_iters <= 0 && !converged && status == 0) status = KAMX_WORLD_MAXITER;
+
+    // ---- natural-map residual of the NCP at the returned y (Eq. 3); the
+    //      product's gather leaves g = J~^T y, which the velocity update uses
+    {
+        const float Dy = sp_apply<NT>(L, R, G, nb, yp);
+        const float vv = Dy + vf;
+        const float gm = sp_gamma(R, mu, vv);
+        const float nm = yp - (vv + gm);
+        const float o = sp_project(R, mu, qe, nm);
+        float lncp = R.kind == kRowPad ? 0.f : fabsf(yp - o);
+        float l1 = 0.f, l2 = 0.f, l3 = 0.f;
+        sp_max3_sum<NT>(lncp, l1, l2, l3, L.red, rbuf);
+        rncp = lncp;
+    }
+
+    L.rf(SRBIAS, tid) = x;
+    L.rf(SRMU, tid) = yp;
+    L.rf(SRREG, tid) = zp;
+    if (tid == 0) {
+        L.s_int[4] = it;
+        L.s_int[5] = status;
+        L.s_int[6] = __float_as_int(rp);
+        L.s_int[7] = __float_as_int(rd);
+        L.s_int[8] = __float_as_int(rc);
+        L.s_int[9] = __float_as_int(rncp);
+    }
+    __syncthreads();
+}
+
+template <int NT>
+__device__ __attribute__((noinline)) void sparse_step_world(KernelArgs *args, int k) {
+    const int tid = threadIdx.x;
+    KernelArgs &a = *uniform_args(args);
+    k = uniform(k);
+    const int w = uniform(a.bucket_worlds[blockIdx.x]);
+    const uint32_t step = (uint32_t)uniform((int)*a.step_ctr) + (uint32_t)k;
+    const WorldInfo W = uniform_world(a.worlds + w);
+    SolverArgs &P = a.p;
+    const SpLds L = sp_views<NT>();
+    int *s_int = L.s_int;
 
     const int nb = W.nb, nj = W.nj;
 
@@ -252,7 +612,7 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
         if (rs && a.stage == 0) a.reset_count[w] += 1;
     }
     __syncthreads();
-    const int reset = s_int[0];
+    const int reset = uniform(s_int[0]);
     if (a.stage == 1) return;  // no feature vector for matrix-free worlds
 
     // ---- bodies (Sec. 3, Eq. 1): state, rotation, inverse mass properties;
@@ -418,7 +778,7 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
         }
     }
     __syncthreads();
-    const int nc = s_int[1];
+    const int nc = uniform(s_int[1]);
     const int row_lim0 = 5 * nj;
     const int row_drv0 = row_lim0 + W.nlim;
     const int row_c0 = row_drv0 + W.ndrv;   // first contact row (compact order)
@@ -555,7 +915,7 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
         R.b = (ab >> 16) - 1;
     }
     if (R.kind != kRowPad && R.a < 0) R.kind = kRowPad;  // defensive: a row needs a body
-    const float bias = L.rf(SRBIAS, tid), mu = L.rf(SRMU, tid), reg = L.rf(SRREG, tid);
+    const float bias = L.rf(SRBIAS, tid), reg = L.rf(SRREG, tid);
     for (int e = 0; e < 12; ++e) Jraw[e] = L.J[e * NT + tid];
     const int qe = (tid - rc0p) & 3;  // lane within a contact quad
     const int ci = tid < row_c0 ? tid : (tid >= rc0p && tid < m_int && qe != 3 ? row_c0 + 3 * ((tid - rc0p) >> 2) + qe : -1);
@@ -565,37 +925,43 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
     {
         constexpr int NWAVE = NT / 64;
         const int lane = tid & 63, wave = tid >> 6;
+        // (every wave keeps all rows' bodies, so a body costs no LDS reads: 25 us
+        // against 61 on the figure)
+        int rows[NWAVE];
+#pragma unroll
+        for (int q = 0; q < NWAVE; ++q) {
+            const int r = 64 * q + lane;
+            rows[q] = r < m_int && L.ri(SRKIND, r) != kRowPad ? L.rab[r] : 0;
+        }
         for (int bb = wave; bb < nb; bb += NWAVE) {
             int cnt = 0;
-            for (int r0 = 0; r0 < m_int; r0 += 64) {
-                const int r = r0 + lane;
-                bool f = false;
-                if (r < m_int && L.ri(SRKIND, r) != kRowPad) {
-                    const int ab = L.rab[r];
-                    f = (ab & 0xffff) - 1 == bb || (ab >> 16) - 1 == bb;
-                }
-                cnt += __popcll(__ballot(f));
-            }
+#pragma unroll
+            for (int q = 0; q < NWAVE; ++q)
+                cnt += __popcll(__ballot((rows[q] & 0xffff) == bb + 1 || rows[q] >> 16 == bb + 1));
             if (lane == 0) L.inc_off[bb + 1] = cnt;
         }
         __syncthreads();
         if (tid == 0) {
             L.inc_off[0] = 0;
-            for (int bb = 0; bb < nb; ++bb) L.inc_off[bb + 1] += L.inc_off[bb];
+            L.rest_off[0] = 0;
+            for (int bb = 0; bb < nb; ++bb) {
+                const int n = L.inc_off[bb + 1];
+                L.inc_off[bb + 1] = L.inc_off[bb] + n;
+                L.rest_off[bb + 1] = L.rest_off[bb] + max(n - sp_held_rows(NT, bb), 0);
+            }
         }
         __syncthreads();
         for (int bb = wave; bb < nb; bb += NWAVE) {
-            int base = L.inc_off[bb];
-            for (int r0 = 0; r0 < m_int; r0 += 64) {
-                const int r = r0 + lane;
-                int side = -1;
-                if (r < m_int && L.ri(SRKIND, r) != kRowPad) {
-                    const int ab = L.rab[r];
-                    if ((ab & 0xffff) - 1 == bb) side = 0;
-                    else if ((ab >> 16) - 1 == bb) side = 1;
-                }
+            int base = 0;
+#pragma unroll
+            for (int q = 0; q < NWAVE; ++q) {
+                const int side = (rows[q] & 0xffff) == bb + 1 ? 0 : (rows[q] >> 16 == bb + 1 ? 1 : -1);
                 const unsigned long long msk = __ballot(side >= 0);
-                if (side >= 0) L.inc_list[base + __popcll(msk & ((1ull << lane) - 1ull))] = (r << 1) | side;
+                if (side >= 0) {
+                    const int k = base + __popcll(msk & ((1ull << lane) - 1ull)), r = 64 * q + lane;
+                    L.inc_list[L.inc_off[bb] + k] = (r << 1) | side;
+                    L.inc_pos[2 * r + side] = k;
+                }
                 base += __popcll(msk);
             }
         }
@@ -637,189 +1003,36 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
     R.preg = p * p * reg;
     __syncthreads();  // raw rows read, incidence lists complete
     for (int e = 0; e < 12; ++e) L.J[e * NT + tid] = R.jt[e];
-    // (rho, 1/rho and the shift change only with the adaptive penalty)
-    float rho = R.kind == kRowBilateral ? P.rho_bil : (R.kind == kRowPad ? 1.f : P.rho_c);
-    float rinv = 1.f / rho;
-    const float eta = P.eta;
-    float shift = eta + rho;  // diagonal of D~ + diag(eta + rho) beyond D~
-    const bool unilateral = R.kind == kRowLimit || R.kind == kRowNormal || R.kind == kRowTangent;
-
-    // ---- warm start (Alg. 1 step 2; Sec. 4.1): y = x = Pi_K(lambda_ws / p),
-    //      z = v~(y) + Gamma(v~(y)) on unilateral rows, 0 on bilateral rows;
-    //      cold: all zero
+    // ---- warm start (Alg. 1 step 2; Sec. 4.1): the impulses the solve starts from
     const int wmode = (reset || P.warmstart == KAMX_WARM_LEARNED) ? KAMX_WARM_COLD : P.warmstart;
-    float x = 0.f, y = 0.f, z = 0.f, Dx = 0.f;
-    if (wmode != KAMX_WARM_COLD) {
-        float lw = 0.f;
-        if (ci >= 0 && ci < m) {
-            if (wmode == KAMX_WARM_EXTERNAL) {
-                lw = a.lambda_ext[W.row_base + ci];
-            } else if (ci < row_c0) {
-                lw = a.lambda[W.row_base + ci];
-            } else {
-                const int c = (ci - row_c0) / 3, e = (ci - row_c0) - 3 * ((ci - row_c0) / 3);
-                const int key = L.ci(SCKEY, c);
-                const int nprev = a.ncontacts_out[w];
-                for (int q = 0; q < nprev && q < kMaxContacts; ++q)
-                    if (a.keys[w * kMaxContacts + q] == key) {
-                        lw = a.lambda[W.row_base + row_c0 + 3 * q + e];
-                        break;
-                    }
-            }
-        }
-        const float ws = (isfinite(lw) && R.kind != kRowPad) ? lw / p : 0.f;
-        y = sp_project(R, mu, qe, ws);
-        x = y;
-        Dx = sp_apply<NT>(L, R, nb, y);
-        const float v0 = Dx + vf;
-        const float gm = sp_gamma(R, mu, v0);
-        z = unilateral ? v0 + gm : 0.f;
-    } else {
-        __syncthreads();  // J~ visible to the gathers
-    }
-    float yh = y, zh = z;  // extrapolated iterates
-    float yp = y, zp = z;  // iterates of the previous iteration
-
-    // ---- PADMM (Alg. 1 steps 3-10) with the x-update (step 5) by Conjugate
-    //      Residual on A = D~ + diag(eta + rho): cr_iters iterations from the
-    //      previous x (Sec. 5.1); A x of the previous iterate is known from
-    //      the residual evaluation, so the solve starts from
-    //      r0 = rhs - A x without a product.
-    float a_k = 1.f, c_prev = INFINITY;
-    int it = 0, status = 0;
-    float rp = 0.f, rd = 0.f, rc = 0.f, rncp = 0.f;
-    const int N = P.fixed_iters > 0 ? P.fixed_iters : P.max_iters;
-    const int ncr = P.cr_iters > 0 ? P.cr_iters : 1;
-    const int n_uni = W.nlim + 3 * nc;  // limit and contact rows: what the adaptive penalty acts on
-    bool converged = false;
-    for (it = 1; it <= N; ++it) {
-        // steps 4-5: s = Gamma(z^), rhs = -v~_f - s + eta x + rho y^ + z^
-        const float s = sp_gamma(R, mu, zh);
-        const float rhs = R.kind == kRowPad ? 0.f : -vf - s + eta * x + rho * yh + zh;
-        float r = rhs - (Dx + shift * x);
-        float pc = r;
-        float Ap = sp_apply<NT>(L, R, nb, r) + shift * r;
-        float sums[4] = {r * Ap, Ap * Ap, 0.f, 0.f};
-        sp_sum<NT, 2>(sums, L.red, rbuf);
-        float rAr = sums[0], ApAp = sums[1];
-        for (int q = 0; q < ncr; ++q) {
-            if (!(ApAp > 0.f) || !(rAr > 0.f)) break;  // exact, or no further progress
-            const float alpha = rAr / ApAp;
-            x += alpha * pc;
-            r -= alpha * Ap;
-            if (q + 1 == ncr) break;
-            const float Ar = sp_apply<NT>(L, R, nb, r) + shift * r;
-            float s3[4] = {r * Ar, Ar * Ar, Ar * Ap, 0.f};
-            sp_sum<NT, 3>(s3, L.red, rbuf);
-            const float beta = s3[0] / rAr;
-            rAr = s3[0];
-            pc = r + beta * pc;
-            Ap = Ar + beta * Ap;
-            ApAp = s3[1] + 2.f * beta * s3[2] + beta * beta * ApAp;
-        }
-        // v~ - v~_f = D~ x for the dual residual and the next right-hand side
-        Dx = sp_apply<NT>(L, R, nb, x);
-        // steps 6-7
-        const float yb = sp_project(R, mu, qe, x - zh * rinv);
-        const float zb = zh - rho * (x - yb);
-        // step 9: residuals (preconditioned units)
-        const float vv = Dx + vf;
-        const float gm = sp_gamma(R, mu, vv);
-        float lrp = fabsf(x - yb);
-        float dres = vv + gm - zb;
-        float lrd = fabsf(dres);
-        if (dres != dres) lrd = dres;
-        // complementarity per unilateral block: y . (v~ + Gamma) over a
-        // contact's quad (every lane takes part in the quad sum), y v~ on a
-        // limit row
-        const bool cont = R.kind == kRowNormal || R.kind == kRowTangent;
-        const float qsum = lane_group_sum<4>(cont ? yb * (vv + gm) : 0.f);
-        float lrc = R.kind == kRowNormal ? fabsf(qsum) : (R.kind == kRowLimit ? fabsf(yb * vv) : 0.f);
-        const float dy = yb - yh, dz = zb - zh;
-        float lcc = R.kind == kRowPad ? 0.f : rho * dy * dy + dz * dz * rinv;
-        if (R.kind == kRowPad) lrp = lrd = 0.f;
-        if (lrp != lrp || lcc != lcc) lrp = NAN;
-        sp_max3_sum<NT>(lrp, lrd, lrc, lcc, L.red, rbuf);
-        rp = lrp;
-        rd = lrd;
-        rc = lrc;
-        // step 8: Nesterov with adaptive restart
-        int restart = 0;
-        float beta = 0.f;
-        if (P.accel) {
-            restart = !(lcc < P.restart_factor * c_prev);
-            if (!restart) {
-                const float a_next = 0.5f * (1.f + sqrtf(1.f + 4.f * a_k * a_k));
-                beta = (a_k - 1.f) / a_next;
-                a_k = a_next;
-                c_prev = lcc;
-            } else {
-                a_k = 1.f;
-                c_prev = c_prev / P.restart_factor;
-            }
-        }
-        if (!P.accel) {
-            yh = yb;
-            zh = zb;
-        } else if (!restart) {
-            yh = yb + beta * (yb - yp);
-            zh = zb + beta * (zb - zp);
+    float lw = 0.f;
+    if (wmode != KAMX_WARM_COLD && ci >= 0 && ci < m) {
+        if (wmode == KAMX_WARM_EXTERNAL) {
+            lw = a.lambda_ext[W.row_base + ci];
+        } else if (ci < row_c0) {
+            lw = a.lambda[W.row_base + ci];
         } else {
-            yh = yp;
-            zh = zp;
-        }
-        yp = yb;
-        zp = zb;
-        // adaptive penalty (not in the paper: residual balancing) at the
-        // checkpoints of a solve that does not exit here; the residuals are
-        // the same in every thread, so the decision is uniform
-        int adapt_dir = 0;
-        if (P.adapt_ratio > 0.f && n_uni > 0 && adapt_checkpoint(it, P.adapt_first) &&
-            !(P.fixed_iters <= 0 && rp < P.eps && rd < P.eps && rc < P.eps)) {
-            if (rd > P.adapt_ratio * rp) adapt_dir = 1;
-            else if (rp > P.adapt_ratio * rd) adapt_dir = 2;
-        }
-        if (tid == 0 && a.rlog && P.log_restarts && it <= P.max_iters)
-            a.rlog[(size_t)w * P.max_iters + (it - 1)] = (uint8_t)(restart | (adapt_dir << 1));
-        if (!(isfinite(rp) && isfinite(rd) && isfinite(rc))) {
-            status = KAMX_WORLD_NONFINITE;
-            break;
-        }
-        if (P.fixed_iters <= 0 && rp < P.eps && rd < P.eps && rc < P.eps) {
-            converged = true;
-            break;
-        }
-        if (adapt_dir) {
-            // the limit and contact rows' penalty changes by the factor (the
-            // operator is applied matrix-free, so nothing is refactored) and
-            // the acceleration restarts at the current (y, z)
-            if (unilateral) {
-                rho *= adapt_dir == 1 ? 1.f / P.adapt_factor : P.adapt_factor;
-                rinv = 1.f / rho;
-                shift = eta + rho;
-            }
-            a_k = 1.f;
-            c_prev = INFINITY;
-            yh = yp;
-            zh = zp;
+            const int c = (ci - row_c0) / 3, e = (ci - row_c0) - 3 * ((ci - row_c0) / 3);
+            const int key = L.ci(SCKEY, c);
+            const int nprev = a.ncontacts_out[w];
+            for (int q = 0; q < nprev && q < kMaxContacts; ++q)
+                if (a.keys[w * kMaxContacts + q] == key) {
+                    lw = a.lambda[W.row_base + row_c0 + 3 * q + e];
+                    break;
+                }
         }
     }
-    if (it > N) it = N;
-    if (P.fixed_iters <= 0 && !converged && status == 0) status = KAMX_WORLD_MAXITER;
-
-    // ---- natural-map residual of the NCP at the returned y (Eq. 3); the
-    //      product's gather leaves g = J~^T y, which the velocity update uses
-    {
-        const float Dy = sp_apply<NT>(L, R, nb, yp);
-        const float vv = Dy + vf;
-        const float gm = sp_gamma(R, mu, vv);
-        const float nm = yp - (vv + gm);
-        const float o = sp_project(R, mu, qe, nm);
-        float lncp = R.kind == kRowPad ? 0.f : fabsf(yp - o);
-        float l1 = 0.f, l2 = 0.f, l3 = 0.f;
-        sp_max3_sum<NT>(lncp, l1, l2, l3, L.red, rbuf);
-        rncp = lncp;
-    }
+    // ---- the solve, with the row's data handed over in LDS
+    L.v[tid] = (isfinite(lw) && R.kind != kRowPad) ? lw / p : 0.f;
+    L.rf(SRBIAS, tid) = vf;
+    L.rf(SRREG, tid) = R.preg;
+    L.ri(SRKIND, tid) = R.kind;
+    __syncthreads();
+    sp_solve<NT>(args, w, nb, rc0p, W.nlim + 3 * nc, wmode != KAMX_WARM_COLD);
+    const float x = L.rf(SRBIAS, tid), yp = L.rf(SRMU, tid), zp = L.rf(SRREG, tid);
+    const int it = s_int[4], status = s_int[5];
+    const float rp = __int_as_float(s_int[6]), rd = __int_as_float(s_int[7]), rc = __int_as_float(s_int[8]),
+                rncp = __int_as_float(s_int[9]);
 
     // ---- outputs: lambda = P y (Alg. 1 step 11) at the compact row index,
     //      statistics, the contact cache
@@ -870,7 +1083,7 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
     //      the rest of the step (dt, or dt / 2 from the Moreau-Jean half step)
     for (int bb = tid; bb < nb; bb += NT) {
         double gy[6];
-        for (int c = 0; c < 6; ++c) gy[c] = L.g[c * kSpBodies + bb];
+        for (int c = 0; c < 6; ++c) gy[c] = L.g[6 * bb + c];
         const double sm = sqrt((double)L.bf(SBIM, bb));
         double Rm[9], t[3], sv[3];
         for (int c = 0; c < 9; ++c) Rm[c] = L.bf(SBR + c, bb);
@@ -897,13 +1110,10 @@ __device__ __attribute__((noinline)) void sparse_step_world(const StepArgs &a, i
 // workgroup keeping its world for all of them (as the dense kernel).
 template <int NT>
 __global__ __launch_bounds__(NT) void sparse_step_kernel(StepArgs a) {
-    __shared__ int s_int[8];
-    __shared__ StepArgs sa;
-    if (threadIdx.x == 0) sa = a;
-    __syncthreads();
+    KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
 #pragma clang loop unroll(disable)
-    for (int k = 0; k < sa.nsteps; ++k) {
-        sparse_step_world<NT>(sa, k, s_int);
+    for (int k = 0; k < a.nsteps; ++k) {
+        sparse_step_world<NT>(args, k);
         __syncthreads();
     }
 }

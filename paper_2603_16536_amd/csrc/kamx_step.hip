@@ -82,17 +82,6 @@ __device__ inline Lds lds_views() {
     return L;
 }
 
-// The launch arguments where the kernel received them: read by scalar loads,
-// they and what follows from them (sizes, branches) are uniform to the compiler
-// and stay out of the vector registers.
-typedef const __attribute__((address_space(4))) StepArgs KernelArgs;
-typedef const __attribute__((address_space(4))) SolverParams SolverArgs;
-
-__device__ inline KernelArgs *uniform_args(KernelArgs *a) {
-    const uint64_t v = (uint64_t)a;
-    return (KernelArgs *)(((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v));
-}
-
 // world-frame rotation of a body (from LDS)
 __device__ inline void body_rot(const Lds &L, int b, float R[9]) {
     for (int k = 0; k < 9; ++k) R[k] = L.bf(BR + k, b);
@@ -1108,13 +1097,7 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
     // read per step (not hoisted out of the caller's step loop)
     const int w = uniform(a.bucket_worlds[blockIdx.x]);
     const uint32_t step = (uint32_t)uniform((int)*a.step_ctr) + (uint32_t)k;
-    WorldInfo W;
-    {
-        const int32_t *src = reinterpret_cast<const int32_t *>(a.worlds + w);
-        int32_t *dst = reinterpret_cast<int32_t *>(&W);
-#pragma unroll
-        for (int e = 0; e < (int)(sizeof(WorldInfo) / 4); ++e) dst[e] = uniform(src[e]);
-    }
+    const WorldInfo W = uniform_world(a.worlds + w);
     SolverArgs &P = a.p;
 
     const Lds L = lds_views<MC>();

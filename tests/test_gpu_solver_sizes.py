@@ -76,3 +76,33 @@ def test_kinematics_at_tile_edges(joints):
     c = max(abs(oracle.joint_coordinate(sg, q, j)[0] - targets[j]) for j in range(scene.n_joints))
     print(f"\n{joints} joints: {it.max()} iterations, constraints {f:.1e}, targets {c:.1e} (bound {bound:.1e})", flush=True)
     assert f < bound and c < bound
+
+
+@pytest.mark.parametrize("kind,n", [("points", 1), ("points", 3), ("points", 4), ("points", 6), ("points", 7),
+                                    ("points", 64), ("joints", 42), ("joints", 43), ("joints", 44)])
+def test_matrix_free_gather_lists(kind, n):
+    """The matrix-free product where a body's list goes past the rows its tasks hold
+    in registers (3 to 192 rows on one body; ten are held, the rest is read in eights),
+    and where there are more gather tasks than threads (more than 42 bodies on 256).
+    The residuals come from the last product D~ x: against FP64 at the returned
+    iterate, on the FP32 Jacobian.  J~ is rounded to FP32 after three operations and the
+    sums are FP64, so with |J~| <= 1 per side and k rows on a body an entry of D~ x is off
+    by at most 8 2^-24 2 k |x|, and v~_f and z by as many roundings of their own."""
+    rng = np.random.default_rng(400 + n)
+    if kind == "points":
+        one, rows = [scenes.box_point_contacts(rng, n, mu=0.5, gap_scale=1e-3) for _ in range(2)], 3 * n
+    else:
+        one, rows = [scenes.random_chain_world(rng, n, with_limits=False, on_manifold=True) for _ in range(2)], 5 * n
+    scene = scenes.round_to_f32(scenes.concat(one))
+    p = dict(dt=1e-3, eta=1e-4, rho_bilateral=1e-4, rho_contact=0.3, fixed_iters=ITERS, max_iters=ITERS, log_restarts=1,
+             linear_solver=kamx.SOLVER_SPARSE, cr_iters=9)
+    g = gpu_step(scene, p)
+    assert g["rows"].tolist() == [rows] * 2
+    assert np.all(g["status"] == 0) and np.all(g["iters"] == ITERS)
+    rs = compare_worlds(scene, kamx.make_params(**p), g, [0, 1], mode="replay", oracle_over=dict(cr_iters=9))
+    it = np.abs(g["iterate"]).max(0)
+    k = rows if kind == "points" else 10
+    bound = 2.0 ** -21 * (2 * k * it[0] + 2 * it[2])
+    d = max(np.abs(r["gpu_resid"][:3] - r["fp64_resid"])[:2].max() for r in rs)
+    print(f"\n{n} {kind}, matrix-free: residuals off by {d:.1e} (bound {bound:.1e})", flush=True)
+    assert d < bound
