@@ -118,8 +118,17 @@ __device__ inline float gelu_grad(float z) {
 
 __device__ inline __bf16 to_bf16(float v) { return (__bf16)v; }
 
-// Device view of a network's parameters (BF16 weights row-major
-// [out][in_pad], FP32 biases and standardisation).
+// Where element (row, col) of a BF16 weight matrix of cols columns (a multiple of 32)
+// lies: blocks of 16 rows x 32 columns, [rows / 16][cols / 32][16][32], so that a
+// matrix-core operand is 1 KB of consecutive memory.  Row-major, a wave's load
+// touched half of sixteen cache lines, and the lines left the L1 before the
+// second half was asked for.
+__host__ __device__ inline long weight_at(int row, int col, int cols) {
+    return ((long)(row >> 4) * (cols >> 5) + (col >> 5)) * 512 + (row & 15) * 32 + (col & 31);
+}
+
+// Device view of a network's parameters (BF16 weights [out][in_pad] in the order
+// of weight_at, FP32 biases and standardisation).
 struct MlpView {
     const __bf16 *w1, *w2, *w3;
     const float *b1, *b2, *b3;

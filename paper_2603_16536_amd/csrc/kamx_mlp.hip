@@ -38,10 +38,16 @@ inline int grad_splits(int M, int N, int K) {
 }
 
 
-// element (i, k) of an operand at p[i * si + k * sk]; one of the strides is 1
+// element (i, k) of an operand at p[i * si + k * sk], one of the strides 1; or of a
+// weight matrix of cols columns, its rows along i (sk = 1) or along k
 struct Operand {
     const __bf16 *p;
     long si, sk;
+    int cols = 0;
+    // where eight elements start that lie side by side: rows r, columns c .. c + 7
+    __device__ const __bf16 *at(long r, long c, long ld) const {
+        return p + (cols ? weight_at((int)r, (int)c, cols) : r * ld + c);
+    }
 };
 
 enum Epilogue { kEpiHidden = 0, kEpiOut = 1, kEpiBackward = 2, kEpiStore = 3 };
@@ -66,11 +72,11 @@ __device__ inline void stage(const Operand &o, long i0, long k0, __bf16 *tile) {
     const int t = threadIdx.x;
     if (o.sk == 1) {
         const int r = t >> 2, kc = (t & 3) * 8;
-        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.p + (i0 + r) * o.si + k0 + kc);
+        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.at(i0 + r, k0 + kc, o.si));
         *reinterpret_cast<bf16x8 *>(tile + r * kLdsRow + kc) = v;
     } else {
         const int k = t >> 3, ic = (t & 7) * 8;
-        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.p + (k0 + k) * o.sk + i0 + ic);
+        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.at(k0 + k, i0 + ic, o.sk));
 #pragma unroll
         for (int j = 0; j < 8; ++j) tile[(ic + j) * kLdsRow + k] = v[j];
     }
@@ -218,7 +224,42 @@ __global__ void sum_slices_kernel(const float *part, long stride, int ns, long n
 struct Layout {
     long oW1, ob1, oW2, ob2, oW3, ob3, total;  // packed FP32 parameters
     long bW1, bW2, bW3, btotal;                // BF16 weight copies
+    long bT2, bT3;                             // transposed ones, [H][H] and [H][op] (0: none)
+    int fp, H, op;
 };
+
+// The BF16 copies of element (r, c) of layer p's weights.
+__device__ inline void store_weight(const Layout &L, int p, int r, int c, float wi, __bf16 *wb) {
+    const __bf16 v = to_bf16(wi);
+    if (p == 0) {
+        wb[L.bW1 + weight_at(r, c, L.fp)] = v;
+    } else if (p == 1) {
+        wb[L.bW2 + weight_at(r, c, L.H)] = v;
+        if (L.bT2) wb[L.bT2 + weight_at(c, r, L.H)] = v;
+    } else {
+        wb[L.bW3 + weight_at(r, c, L.H)] = v;
+        if (L.bT3) wb[L.bT3 + weight_at(c, r, L.op)] = v;
+    }
+}
+
+// The same for parameter i, where it is a weight.
+__device__ inline void store_bf16(const Layout &L, long i, float wi, __bf16 *wb) {
+    const int p = i >= L.oW3 ? 2 : (i >= L.oW2 ? 1 : 0);
+    const long k = i - (p == 2 ? L.oW3 : (p == 1 ? L.oW2 : L.oW1));
+    const int cols = p ? L.H : L.fp, r = (int)(k / cols);
+    if (r < (p == 2 ? L.op : L.H)) store_weight(L, p, r, (int)(k - (long)r * cols), wi, wb);
+}
+
+// One bias-corrected Adam update of parameter i by its gradient.
+__device__ inline float adam_update(float *w, float *m, float *v, long i, float gi, float lr, float c1, float c2) {
+    const float mi = 0.9f * m[i] + 0.1f * gi;
+    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
+    m[i] = mi;
+    v[i] = vi;
+    const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+    w[i] = wi;
+    return wi;
+}
 
 // Bias-corrected Adam on the packed FP32 parameters; weights also refresh
 // their BF16 copies.
@@ -226,28 +267,13 @@ __global__ void adam_kernel(float *w, const float *g, float *m, float *v, long n
                             Layout L, __bf16 *wb) {
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    float gi = g[i];
-    float mi = 0.9f * m[i] + 0.1f * gi;
-    float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
-    w[i] = wi;
-    long bi = -1;
-    if (i >= L.oW1 && i < L.ob1) bi = L.bW1 + (i - L.oW1);
-    else if (i >= L.oW2 && i < L.ob2) bi = L.bW2 + (i - L.oW2);
-    else if (i >= L.oW3 && i < L.ob3) bi = L.bW3 + (i - L.oW3);
-    if (bi >= 0) wb[bi] = to_bf16(wi);
+    store_bf16(L, i, adam_update(w, m, v, i, g[i], lr, c1, c2), wb);
 }
 
 __global__ void refresh_bf16_kernel(const float *w, Layout L, __bf16 *wb) {
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= L.total) return;
-    long bi = -1;
-    if (i >= L.oW1 && i < L.ob1) bi = L.bW1 + (i - L.oW1);
-    else if (i >= L.oW2 && i < L.ob2) bi = L.bW2 + (i - L.oW2);
-    else if (i >= L.oW3 && i < L.ob3) bi = L.bW3 + (i - L.oW3);
-    if (bi >= 0) wb[bi] = to_bf16(w[i]);
+    store_bf16(L, i, w[i], wb);
 }
 
 // s = 1 / sigma (0 for constant features); sigma_out floored at 1e-12 -> 1.
@@ -264,6 +290,431 @@ __global__ void set_norm_kernel(const float *mu_in, const float *sd_in, int n_in
         mu_o[i] = mu_out[i];
         sd_o[i] = sd > 1e-12f ? sd : 1.f;
     }
+}
+
+// ---- rows of the batch through the whole network ---------------------------
+//
+// A layer of this network is small (the biped's: 704 x 256, 256 x 256, 256 x 256)
+// and a product of its own per layer is launch and load latency: 41 us for a
+// batch of 1000 in four launches of 64-row tiles that waited for memory twice per
+// 32 of K.  Instead a workgroup takes 16 or 32 rows through every layer, and in
+// training back again: activations stay in LDS as BF16 operands, the
+// pre-activations' FP32 values in the registers of the lanes that computed them,
+// and weights come from L2 straight into operand registers, four steps of K ahead
+// (eight ahead, or every line touched at the start, gained nothing).  Every sum over
+// K runs in the order of gemm_kernel, so outputs have its bits.  17.5 us for the
+// batch of 1000: 4 standardising, 3 in the first layer's weights, 3.5 in each of the
+// two layers of error functions; a training batch of 4096 takes 34 us.
+
+constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
+constexpr int kRowTiles = 4;  // hidden column tiles a wave keeps, at most
+constexpr int kAhead = 4;     // steps of K loaded ahead
+constexpr int kRowLine = 256;  // workgroups of 16 rows, at most
+constexpr size_t kRowLds = 65536 - 64;  // of dynamic LDS, besides the static partial sums
+
+struct RowArgs {
+    const float *x;
+    long ldx;
+    int batch, n_in, fp, H, n_out, op, R;
+    const float *mu_in, *s_in, *mu_out, *sd_out;
+    const __bf16 *w1, *w2, *w3, *w2t, *w3t;
+    const float *b1, *b2, *b3;
+    float *y;  // prediction
+    long ldy;
+    // training: targets, activations and their gradients as operands of the weight
+    // gradients ([R / 32][columns][32 rows]), the gradients' FP32 values [R][columns]
+    // for the bias gradients, and the squared error per workgroup
+    const float *t;
+    __bf16 *xk, *h1k, *h2k, *dyk, *dz2k, *dz1k;
+    float *dy, *dz2, *dz1, *loss_part;
+};
+
+__host__ __device__ inline int row_lda(int fp, int H) { return (fp > H ? fp : H) + 8; }
+__host__ __device__ inline int row_ldb(int H, int op, bool train) { return (train && op > H ? op : H) + 8; }
+
+inline size_t row_lds_bytes(int fp, int H, int op, int mb, bool train) {
+    return sizeof(__bf16) * 16 * mb * (size_t)(row_lda(fp, H) + row_ldb(H, op, train));
+}
+
+// Networks whose rows fit 64 KB of LDS and whose hidden columns fit the registers;
+// wider ones go through one product per layer.
+inline bool rows_kernel_takes(int fp, int H, int op) {
+    return H <= 16 * kRowTiles * kRowWaves && row_lds_bytes(fp, H, op, 1, true) <= kRowLds;
+}
+
+// Weights of up to TN column tiles on their way from L2: kAhead steps of K.  The first
+// steps of a layer are asked for before the layer in front of it has ended.
+template <int TN>
+struct Weights {
+    const __bf16 *w[TN];
+    int K;
+    bf16x8 b[kAhead][TN];
+    // W [n][K] in the order of weight_at, K a multiple of 64
+    __device__ inline void begin(const __bf16 *W, int K_, const int (&tile)[TN]) {
+        const int lane = threadIdx.x & 63;
+        K = K_;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) w[j] = W + (long)tile[j] * (K >> 5) * 512 + (lane & 15) * 32 + (lane >> 4) * 8;
+        load(0);
+    }
+    __device__ inline void load(int k0) {
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int k = (min(k0 + kTileK * q, K - kTileK) >> 5) * 512;  // (past the end: not used)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) b[q][j] = *reinterpret_cast<const bf16x8 *>(w[j] + k);
+        }
+    }
+};
+
+// acc[i][j] = sum over k of act(16 i + row, k) W(16 tile[j] + column, k); act in LDS
+// (row stride ld).
+template <int MB, int TN>
+__device__ inline void rows_times(const __bf16 *act, int ld, Weights<TN> &W, floatx4 (&acc)[MB][TN]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const __bf16 *a0 = act + (lane & 15) * ld + (lane >> 4) * 8;
+    for (int k0 = 0; k0 < W.K; k0 += kTileK * kAhead) {
+        bf16x8 c[kAhead][TN];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) c[q][j] = W.b[q][j];
+        if (k0 + kTileK * kAhead < W.K) W.load(k0 + kTileK * kAhead);
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            if (k0 + kTileK * q >= W.K) break;
+            bf16x8 av[MB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) av[i] = *reinterpret_cast<const bf16x8 *>(a0 + 16 * i * ld + k0 + kTileK * q);
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], c[q][j], acc[i][j], 0, 0, 0);
+        }
+    }
+}
+
+using bf16x4 = __bf16 __attribute__((ext_vector_type(4)));
+
+// Four consecutive rows (from m, a multiple of 4) of column c, as an operand of a
+// sum over the rows.
+__device__ inline void store_k(__bf16 *o, int cols, long m, int c, bf16x4 v) {
+    *reinterpret_cast<bf16x4 *>(o + ((m >> 5) * cols + c) * 32 + (m & 31)) = v;
+}
+
+template <int MB, int TN, bool TRAIN>
+__global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
+    extern __shared__ float4 row_lds[];
+    __shared__ float red[kRowWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rg = (lane >> 4) * 4, fr = lane & 15;
+    constexpr int kRows = 16 * MB;
+    const long m0 = (long)blockIdx.x * kRows;
+    const int lda = row_lda(a.fp, a.H), ldb = row_ldb(a.H, a.op, TRAIN);
+    __bf16 *P = reinterpret_cast<__bf16 *>(row_lds), *Q = P + kRows * lda;
+    const int H = a.H, ht = H / 16, ot = a.op / 16;
+
+    int tile[TN];
+    bool mine[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        mine[j] = wave + kRowWaves * j < ht;
+        tile[j] = min(wave + kRowWaves * j, ht - 1);
+    }
+    Weights<TN> W;
+    W.begin(a.w1, a.fp, tile);
+
+    // x^ = (x - mu) s in BF16, zero in padded rows and columns: a wave's 2 MB rows
+    // together, four loads of each in flight
+    constexpr int kWaveRows = kRows / kRowWaves, kLoads = 4;
+    for (int c0 = lane; c0 < a.fp; c0 += 64 * kLoads) {
+        float v[kWaveRows][kLoads], mu[kLoads], sd[kLoads];
+#pragma unroll
+        for (int e = 0; e < kLoads; ++e) {
+            const int c = min(c0 + 64 * e, a.n_in - 1);
+            mu[e] = a.mu_in[c];
+            sd[e] = a.s_in[c];
+#pragma unroll
+            for (int q = 0; q < kWaveRows; ++q)
+                v[q][e] = a.x[min(m0 + wave + kRowWaves * q, (long)a.batch - 1) * a.ldx + c];
+        }
+#pragma unroll
+        for (int e = 0; e < kLoads; ++e) {
+            const int c = c0 + 64 * e;
+            if (c >= a.fp) break;
+#pragma unroll
+            for (int q = 0; q < kWaveRows; ++q) {
+                const int r = wave + kRowWaves * q;
+                P[r * lda + c] = to_bf16(m0 + r < a.batch && c < a.n_in ? (v[q][e] - mu[e]) * sd[e] : 0.f);
+            }
+        }
+    }
+    __syncthreads();
+    if (TRAIN)
+        for (int i = threadIdx.x; i < a.fp * (kRows / 4); i += kRowThreads) {
+            const int c = i / (kRows / 4), r = 4 * (i % (kRows / 4));
+            const bf16x4 v = {P[r * lda + c], P[(r + 1) * lda + c], P[(r + 2) * lda + c], P[(r + 3) * lda + c]};
+            store_k(a.xk, a.fp, m0 + r, c, v);
+        }
+
+    // z = act W^T + b; gelu(z) to LDS
+    floatx4 acc[MB][TN], z1[MB][TN], z2[MB][TN];
+    auto hidden = [&](const float *bias, floatx4 (&z)[MB][TN], __bf16 *h, int ld, __bf16 *hk) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = 16 * tile[j] + fr;
+            const float b = bias[n];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                bf16x4 o;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float zv = acc[i][j][c] + b;
+                    z[i][j][c] = zv;
+                    o[c] = to_bf16(gelu(zv));
+                }
+                if (mine[j]) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) h[(16 * i + rg + c) * ld + n] = o[c];
+                    if (TRAIN) store_k(hk, H, m0 + 16 * i + rg, n, o);
+                }
+            }
+        }
+    };
+    rows_times<MB, TN>(P, lda, W, acc);
+    W.begin(a.w2, H, tile);
+    hidden(a.b1, z1, Q, ldb, a.h1k);
+    __syncthreads();
+    rows_times<MB, TN>(Q, ldb, W, acc);
+    int otile[TN];
+    auto out_tiles = [&](int t0) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) otile[j] = min(t0 + kRowWaves * j, ot - 1);
+        W.begin(a.w3, H, otile);
+    };
+    out_tiles(wave);
+    hidden(a.b2, z2, P, lda, a.h2k);
+    __syncthreads();
+
+    // outputs, in training their gradients of the mean squared error
+    float sq = 0.f;
+    for (int t0 = wave; t0 < ot; t0 += kRowWaves * TN) {
+        if (t0 != wave) out_tiles(t0);
+        rows_times<MB, TN>(P, lda, W, acc);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            if (t0 + kRowWaves * j >= ot) break;
+            const int n = 16 * otile[j] + fr;
+            const float b = a.b3[n];
+            const bool real = n < a.n_out;
+            const float mu = real ? a.mu_out[n] : 0.f, sd = real ? a.sd_out[n] : 1.f;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                bf16x4 o;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const long m = m0 + 16 * i + rg + c;
+                    const float yn = acc[i][j][c] + b;
+                    if (TRAIN) {
+                        float g = 0.f;
+                        if (real && m < a.batch) {
+                            const float tn = (a.t[m * a.n_out + n] - mu) / sd;
+                            const float err = yn - tn;
+                            sq += err * err;
+                            g = 2.f * err / ((float)a.batch * (float)a.n_out);
+                        }
+                        a.dy[m * a.op + n] = g;
+                        o[c] = to_bf16(g);
+                        Q[(16 * i + rg + c) * ldb + n] = o[c];
+                    } else if (real && m < a.batch) {
+                        a.y[m * a.ldy + n] = __builtin_fmaf(sd, yn, mu);
+                    }
+                }
+                if (TRAIN) store_k(a.dyk, a.op, m0 + 16 * i + rg, n, o);
+            }
+        }
+    }
+    if (!TRAIN) return;
+    W.begin(a.w3t, a.op, tile);
+    for (int o = 1; o < 64; o <<= 1) sq += __shfl_xor(sq, o);
+    if (lane == 0) red[wave] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float s = 0.f;
+        for (int k = 0; k < kRowWaves; ++k) s += red[k];
+        a.loss_part[blockIdx.x] = s;
+    }
+
+    // dz = (d W) gelu'(z)
+    auto back = [&](const floatx4 (&z)[MB][TN], __bf16 *d, float *d32, __bf16 *dk) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            if (!mine[j]) break;
+            const int n = 16 * tile[j] + fr;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                bf16x4 o;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float dz = acc[i][j][c] * gelu_grad(z[i][j][c]);
+                    d32[(m0 + 16 * i + rg + c) * H + n] = dz;
+                    o[c] = to_bf16(dz);
+                    if (d) d[(16 * i + rg + c) * lda + n] = o[c];
+                }
+                store_k(dk, H, m0 + 16 * i + rg, n, o);
+            }
+        }
+    };
+    rows_times<MB, TN>(Q, ldb, W, acc);
+    W.begin(a.w2t, H, tile);
+    back(z2, P, a.dz2, a.dz2k);
+    __syncthreads();
+    rows_times<MB, TN>(P, lda, W, acc);
+    back(z1, nullptr, a.dz1, a.dz1k);
+}
+
+// The gradients of a training step and Adam's update in one launch: 24 us for a
+// batch of 4096, where a product, a sum of its slices, two passes of column sums per
+// layer and the update were thirteen launches and about 120 us.  A workgroup owns a
+// 32 x 32 tile of a layer's weights: C[M, N] = sum over the rows of A(m, row) B(n, row),
+// operands as rows_kernel writes them (1 KB of consecutive memory each).  Its 16 waves
+// take a slice of the rows each, and the slices are added in order from LDS; through
+// global memory their partial results were 28 MB written and read.  8 columns of
+// the biases' sums are another workgroup's, in kColBlocks row ranges of four
+// interleaved groups.
+struct GradArgs {
+    const __bf16 *A[3], *B[3];
+    const float *d[3];
+    int M[3], N[3], ns[3], first[3], col_first[3];  // first: a product's first workgroup
+    int R, cols, loss_blocks;
+    float *w, *g, *m, *v;
+    float lr, c1, c2, loss_scale;
+    const float *loss_part;
+    float *loss;
+    Layout L;
+    __bf16 *wb;
+};
+
+constexpr int kGradWaves = 16;
+static_assert(2 * kGradWaves == kColBlocks, "a thread per column, row group and row range");
+
+__global__ __launch_bounds__(64 * kGradWaves) void grads_kernel(GradArgs g) {
+    __shared__ float part[kGradWaves][1024];
+    const Layout &L = g.L;
+    const int bx = (int)blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (bx < g.loss_blocks) {
+        float s = 0.f;
+        for (int k = tid; k < g.R / 16; k += 64 * kGradWaves) s += g.loss_part[k];
+        part[0][tid] = s;
+        __syncthreads();
+        for (int k = 32 * kGradWaves; k > 0; k >>= 1) {
+            if (tid < k) part[0][tid] += part[0][tid + k];
+            __syncthreads();
+        }
+        if (tid == 0) g.loss[0] = part[0][0] * g.loss_scale;
+        return;
+    }
+    if (bx < g.first[0]) {
+        // thread: column, row group, row range (neighbouring columns on one XCD: they share
+        // cache lines)
+        const int b = bx - g.loss_blocks, col = 8 * ((b & 7) * (g.cols / 64) + (b >> 3)) + (tid & 7);
+        const int grp = (tid >> 3) & 3, y = tid >> 5;
+        const int p = col >= g.col_first[2] ? 2 : (col >= g.col_first[1] ? 1 : 0);
+        const int n = g.M[p], c = col - g.col_first[p], span = g.R / kColBlocks, rows = (span - grp + 3) / 4;
+        const float *d = g.d[p] + (long)(y * span + grp) * n + c;
+        float s = 0.f;
+        for (int r = 0; r < rows; r += 16) {
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = d[4l * min(r + q, rows - 1) * n];
+            __builtin_amdgcn_sched_barrier(0);  // (all loads in flight)
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                if (r + q < rows) s += v[q];
+        }
+        part[0][tid] = s;
+        __syncthreads();
+        if (tid < 8) {
+            float t = 0.f;
+#pragma unroll
+            for (int k = 0; k < kColBlocks; ++k) {
+                const float *q = &part[0][32 * k + tid];
+                t += (q[0] + q[8]) + (q[16] + q[24]);
+            }
+            const long i = (p == 2 ? L.ob3 : (p == 1 ? L.ob2 : L.ob1)) + c;
+            g.g[i] = t;
+            adam_update(g.w, g.m, g.v, i, t, g.lr, g.c1, g.c2);
+        }
+        return;
+    }
+    const int p = bx >= g.first[2] ? 2 : (bx >= g.first[1] ? 1 : 0);
+    const int M = g.M[p], N = g.N[p], tn = N / 32, at = bx - g.first[p];
+    // (workgroups go round the eight XCDs: a row of tiles on one, so that its L2 holds
+    // the row's operand)
+    const bool rows8 = (M / 32) % 8 == 0;
+    const int tm = rows8 ? (at & 7) + 8 * ((at >> 3) / tn) : at / tn, tc = rows8 ? (at >> 3) % tn : at % tn;
+    const int off = (lane & 15) * 32 + (lane >> 4) * 8, ns = g.ns[p], nk = g.R / kTileK / ns;
+    const __bf16 *A = g.A[p] + (long)tm * 1024 + off, *B = g.B[p] + (long)tc * 1024 + off;
+    // this thread's element of the tile
+    const int em = tid >> 5, en = tid & 31;
+    auto place = [](int m, int n) { return 32 * m + (n ^ ((m & 4) << 2)); };  // (rows 4 apart in other banks)
+    float total = ns > 1 ? 0.f : -0.f;
+    for (int s0 = 0; s0 < ns; s0 += kGradWaves) {
+        const int slice = s0 + wave;
+        if (slice < ns) {
+            floatx4 acc[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            const int k1 = (slice + 1) * nk;
+            for (int k = slice * nk; k < k1; k += kAhead) {
+                bf16x8 fa[kAhead][2], fb[kAhead][2];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    const long kk = min(k + q, k1 - 1);  // (past the end: not used)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        fa[q][i] = *reinterpret_cast<const bf16x8 *>(A + (kk * M + 16 * i) * 32);
+                        fb[q][i] = *reinterpret_cast<const bf16x8 *>(B + (kk * N + 16 * i) * 32);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);  // (all loads in flight)
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    if (k + q >= k1) break;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[q][i], fb[q][j], acc[i][j], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        part[wave][place(16 * i + (lane >> 4) * 4 + c, 16 * j + (lane & 15))] = acc[i][j][c];
+        }
+        __syncthreads();
+        float e[kGradWaves];
+#pragma unroll
+        for (int k = 0; k < kGradWaves; ++k) e[k] = part[k][place(em, en)];
+#pragma unroll
+        for (int k = 0; k < kGradWaves; ++k)
+            if (s0 + k < ns) total += e[k];
+        __syncthreads();
+    }
+    const int r = 32 * tm + em, c = 32 * tc + en;
+    const long i = (p == 2 ? L.oW3 : (p == 1 ? L.oW2 : L.oW1)) + (long)r * N + c;
+    g.g[i] = total;
+    store_weight(L, p, r, c, adam_update(g.w, g.m, g.v, i, total, g.lr, g.c1, g.c2), g.wb);
 }
 
 inline int pad64(int n) { return (n + 63) / 64 * 64; }
@@ -285,6 +736,7 @@ struct kamx_mlp_s {
     float *partial = nullptr;
     float *ws = nullptr;  // partial sums of split weight gradients and bias gradients
     long ws_floats = 0;
+    bool fused = false;  // the row kernel takes this network
     std::vector<void *> allocs;
 };
 
@@ -352,6 +804,15 @@ extern "C" kamx_status kamx_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n
     L.bW2 = H * fp;
     L.bW3 = L.bW2 + H * H;
     L.btotal = L.bW3 + op * H;
+    L.fp = n->fp;
+    L.H = n->H;
+    L.op = n->op;
+    n->fused = rows_kernel_takes(n->fp, n->H, n->op);
+    if (n->fused) {
+        L.bT2 = L.btotal;
+        L.bT3 = L.bT2 + H * H;
+        L.btotal = L.bT3 + H * op;
+    }
 #define C_TRY(expr)                      \
     do {                                 \
         kamx_status s_ = (expr);         \
@@ -376,25 +837,28 @@ extern "C" kamx_status kamx_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n
     C_TRY(mlp_alloc(n, &n->dyb, R * op));
     C_TRY(mlp_alloc(n, &n->dz2b, R * H));
     C_TRY(mlp_alloc(n, &n->dz1b, R * H));
-    C_TRY(mlp_alloc(n, &n->z1, R * H));
-    C_TRY(mlp_alloc(n, &n->z2, R * H));
-    C_TRY(mlp_alloc(n, &n->yn, R * op));
+    if (!n->fused) {
+        C_TRY(mlp_alloc(n, &n->z1, R * H));
+        C_TRY(mlp_alloc(n, &n->z2, R * H));
+        C_TRY(mlp_alloc(n, &n->yn, R * op));
+        C_TRY(mlp_alloc(n, &n->partial, (R * std::max<long>(op, 1) + 255) / 256));
+    }
     C_TRY(mlp_alloc(n, &n->dy, R * op));
     C_TRY(mlp_alloc(n, &n->dz2, R * H));
     C_TRY(mlp_alloc(n, &n->dz1, R * H));
-    C_TRY(mlp_alloc(n, &n->partial, (R * std::max<long>(op, 1) + 255) / 256));
     {
         // split-K weight gradients: each of M x N outputs gets up to
         // grad_splits(...) partials for the padded batch K of a training
         // call (any multiple of 64 up to the capacity: a smaller batch can
         // take more slices than the capacity itself); bias gradients up to
-        // kColBlocks
+        // kColBlocks.  The fused step only leaves its row blocks' losses
         long most = (long)kColBlocks * std::max(H, op);
-        for (long K = 64; K <= R; K += 64) {
+        for (long K = 64; K <= R && !n->fused; K += 64) {
             const long a = (long)grad_splits(op, H, (int)K) * op * H, b = (long)grad_splits(H, H, (int)K) * H * H,
                        c = (long)grad_splits(H, fp, (int)K) * H * fp;
             most = std::max(most, std::max(a, std::max(b, c)));
         }
+        if (n->fused) most = R / 16;
         n->ws_floats = most;
         C_TRY(mlp_alloc(n, &n->ws, n->ws_floats));
     }
@@ -496,6 +960,124 @@ static hipError_t colsum(kamx_mlp n, const float *a, int rows, int cols, float *
     return hipGetLastError();
 }
 
+static RowArgs row_args(kamx_mlp n, const float *x, long ldx, int batch) {
+    const Layout &L = n->L;
+    RowArgs r{};
+    r.x = x;
+    r.ldx = ldx;
+    r.batch = batch;
+    r.n_in = n->n_in;
+    r.fp = n->fp;
+    r.H = n->H;
+    r.n_out = n->n_out;
+    r.op = n->op;
+    r.R = pad64(batch);
+    r.mu_in = n->mu_in;
+    r.s_in = n->s_in;
+    r.mu_out = n->mu_out;
+    r.sd_out = n->sd_out;
+    r.w1 = n->wb + L.bW1;
+    r.w2 = n->wb + L.bW2;
+    r.w3 = n->wb + L.bW3;
+    r.w2t = n->wb + L.bT2;
+    r.w3t = n->wb + L.bT3;
+    r.b1 = n->w + L.ob1;
+    r.b2 = n->w + L.ob2;
+    r.b3 = n->w + L.ob3;
+    return r;
+}
+
+template <int MB, int TN, bool TRAIN>
+static hipError_t launch_rows_tn(const RowArgs &r, hipStream_t s) {
+    const size_t lds = row_lds_bytes(r.fp, r.H, r.op, MB, TRAIN);
+    if (MB > 1) {
+        static bool configured = false;
+        if (!configured) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rows_kernel<MB, TN, TRAIN>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)(MB * kRowLds));
+            if (e != hipSuccess) return e;
+            configured = true;
+        }
+    }
+    hipLaunchKernelGGL((rows_kernel<MB, TN, TRAIN>), dim3((unsigned)(r.R / (16 * MB))), dim3(kRowThreads), lds, s, r);
+    return hipGetLastError();
+}
+
+template <int MB, bool TRAIN>
+static hipError_t launch_rows_mb(const RowArgs &r, hipStream_t s) {
+    switch ((r.H + 16 * kRowWaves - 1) / (16 * kRowWaves)) {
+    case 1: return launch_rows_tn<MB, 1, TRAIN>(r, s);
+    case 2: return launch_rows_tn<MB, 2, TRAIN>(r, s);
+    case 3: return launch_rows_tn<MB, 3, TRAIN>(r, s);
+    case 4: return launch_rows_tn<MB, 4, TRAIN>(r, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// A prediction takes 16 rows a workgroup while that is not more than one workgroup per
+// CU, then 32, which halves the weights' traffic: on the biped's network 17.8 us
+// against 20.5 for 4096 rows, but 29.4 against 23.3 for 8192.  (Training keeps two
+// layers' pre-activations in registers and takes 16.)
+static hipError_t predict_rows(const RowArgs &r, hipStream_t s) {
+    return r.R > 16 * kRowLine ? launch_rows_mb<2, false>(r, s) : launch_rows_mb<1, false>(r, s);
+}
+
+// One training step: rows forward and back, weight gradients, update.
+static hipError_t train_fused(kamx_mlp n, const float *x, const float *target, int batch, float lr, float *loss,
+                              hipStream_t s) {
+    const Layout &L = n->L;
+    const int H = n->H, fp = n->fp, op = n->op, R = pad64(batch);
+    RowArgs r = row_args(n, x, n->n_in, batch);
+    r.t = target;
+    r.xk = n->xh;
+    r.h1k = n->h1;
+    r.h2k = n->h2;
+    r.dyk = n->dyb;
+    r.dz2k = n->dz2b;
+    r.dz1k = n->dz1b;
+    r.dy = n->dy;
+    r.dz2 = n->dz2;
+    r.dz1 = n->dz1;
+    r.loss_part = n->ws;
+    hipError_t e = launch_rows_mb<1, true>(r, s);
+    if (e != hipSuccess) return e;
+    // (layer order of the parameters)
+    const __bf16 *A[3] = {n->dz1b, n->dz2b, n->dyb}, *B[3] = {n->xh, n->h1, n->h2};
+    const float *d[3] = {n->dz1, n->dz2, n->dy};
+    GradArgs g{};
+    g.loss_blocks = loss ? 1 : 0;
+    g.cols = 2 * H + op;
+    int wgs = g.loss_blocks + g.cols / 8, col = 0;
+    for (int p = 0; p < 3; ++p) {
+        const int M = p < 2 ? H : op, N = p ? H : fp;
+        g.A[p] = A[p];
+        g.B[p] = B[p];
+        g.d[p] = d[p];
+        g.M[p] = M;
+        g.N[p] = N;
+        g.ns[p] = grad_splits(M, N, R);
+        g.first[p] = wgs;
+        g.col_first[p] = col;
+        wgs += (M / 32) * (N / 32);
+        col += M;
+    }
+    g.R = R;
+    g.w = n->w;
+    g.g = n->g;
+    g.m = n->am;
+    g.v = n->av;
+    g.lr = lr;
+    g.c1 = (float)(1.0 - pow(0.9, n->t));
+    g.c2 = (float)(1.0 - pow(0.999, n->t));
+    g.loss_scale = 1.f / ((float)batch * (float)n->n_out);
+    g.loss_part = n->ws;
+    g.loss = loss;
+    g.L = L;
+    g.wb = n->wb;
+    hipLaunchKernelGGL(grads_kernel, dim3(wgs), dim3(64 * kGradWaves), 0, s, g);
+    return hipGetLastError();
+}
+
 // Activations of one forward pass: the normalised BF16 input, the two
 // BF16 hidden activations and, for training, the FP32 pre-activations and
 // normalised outputs (null when only the prediction is wanted).
@@ -510,6 +1092,13 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
                                     long ldy, hipStream_t s) {
     const int R = pad64(batch), H = n->H, fp = n->fp, op = n->op;
     const Layout &L = n->L;
+    if (n->fused && !a.z1) {
+        RowArgs r = row_args(n, x, ldx, batch);
+        r.y = y;
+        r.ldy = ldy;
+        MLP_HIP(predict_rows(r, s));
+        return KAMX_OK;
+    }
     long cnt = (long)R * fp;
     hipLaunchKernelGGL(normalise_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, x, ldx, batch, n->n_in,
                        n->mu_in, n->s_in, a.xh, R, fp);
@@ -519,11 +1108,11 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
     e.f32 = a.z1;
     e.b16 = a.h1;
     e.ld = H;
-    MLP_HIP((gemm<kEpiHidden>(Operand{a.xh, fp, 1}, Operand{n->wb + L.bW1, fp, 1}, R, H, fp, e, s)));
+    MLP_HIP((gemm<kEpiHidden>(Operand{a.xh, fp, 1}, Operand{n->wb + L.bW1, fp, 1, fp}, R, H, fp, e, s)));
     e.bias = n->w + L.ob2;
     e.f32 = a.z2;
     e.b16 = a.h2;
-    MLP_HIP((gemm<kEpiHidden>(Operand{a.h1, H, 1}, Operand{n->wb + L.bW2, H, 1}, R, H, H, e, s)));
+    MLP_HIP((gemm<kEpiHidden>(Operand{a.h1, H, 1}, Operand{n->wb + L.bW2, H, 1, H}, R, H, H, e, s)));
     EpiArgs o{};
     o.bias = n->w + L.ob3;
     o.f32 = a.yn;
@@ -534,7 +1123,7 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
     o.n_out = n->n_out;
     o.mu = n->mu_out;
     o.sigma = n->sd_out;
-    MLP_HIP((gemm<kEpiOut>(Operand{a.h2, H, 1}, Operand{n->wb + L.bW3, H, 1}, R, op, H, o, s)));
+    MLP_HIP((gemm<kEpiOut>(Operand{a.h2, H, 1}, Operand{n->wb + L.bW3, H, 1, H}, R, op, H, o, s)));
     return KAMX_OK;
 }
 
@@ -648,6 +1237,11 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int R = pad64(batch), H = n->H, fp = n->fp, op = n->op;
     const Layout &L = n->L;
+    if (n->fused) {
+        n->t += 1;
+        MLP_HIP(train_fused(n, x, y_target, batch, lr, loss_dev, s));
+        return KAMX_OK;
+    }
     kamx_status st = mlp_forward_rows(n, own_acts(n, true), x, n->n_in, batch, nullptr, 0, s);
     if (st != KAMX_OK) return st;
     const long cnt = (long)R * op;
@@ -669,7 +1263,7 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     e.f32 = n->dz2;
     e.b16 = n->dz2b;
     e.ld = H;
-    MLP_HIP((gemm<kEpiBackward>(Operand{n->dyb, op, 1}, Operand{n->wb + L.bW3, 1, H}, R, H, op, e, s)));
+    MLP_HIP((gemm<kEpiBackward>(Operand{n->dyb, op, 1}, Operand{n->wb + L.bW3, 1, H, H}, R, H, op, e, s)));
     // layer 2
     MLP_HIP(gemm_store(n, Operand{n->dz2b, 1, H}, Operand{n->h1, 1, H}, H, H, R, n->g + L.oW2, s));
     MLP_HIP(colsum(n, n->dz2, R, H, n->g + L.ob2, s));
@@ -678,7 +1272,7 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     e.f32 = n->dz1;
     e.b16 = n->dz1b;
     e.ld = H;
-    MLP_HIP((gemm<kEpiBackward>(Operand{n->dz2b, H, 1}, Operand{n->wb + L.bW2, 1, H}, R, H, H, e, s)));
+    MLP_HIP((gemm<kEpiBackward>(Operand{n->dz2b, H, 1}, Operand{n->wb + L.bW2, 1, H, H}, R, H, H, e, s)));
     // layer 1
     MLP_HIP(gemm_store(n, Operand{n->dz1b, 1, H}, Operand{n->xh, 1, fp}, H, fp, R, n->g + L.oW1, s));
     MLP_HIP(colsum(n, n->dz1, R, H, n->g + L.ob1, s));

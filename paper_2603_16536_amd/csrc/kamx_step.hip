@@ -1244,11 +1244,19 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
         auto layer = [&](const __bf16 *x, int K, const __bf16 *Wt, int nout_pad, auto &&epilogue) {
             for (int t = wv; t < nout_pad / 16; t += NW) {
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                const __bf16 *wrow = Wt + (long)(16 * t + fr) * K + fk;
-                for (int k0 = 0; k0 < K; k0 += 32) {
-                    const bf16x8 av = fr == 0 ? *reinterpret_cast<const bf16x8 *>(x + k0 + fk) : zero8;
-                    const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(wrow + k0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
+                const __bf16 *wt = Wt + (long)t * (K >> 5) * 512 + fr * 32 + fk;
+                constexpr int kAhead = 8;  // steps of K loaded together
+                for (int k0 = 0; k0 < K; k0 += 32 * kAhead) {
+                    bf16x8 bv[kAhead];
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q)
+                        bv[q] = *reinterpret_cast<const bf16x8 *>(wt + (min(k0 + 32 * q, K - 32) >> 5) * 512);
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q) {
+                        if (k0 + 32 * q >= K) break;
+                        const bf16x8 av = fr == 0 ? *reinterpret_cast<const bf16x8 *>(x + k0 + 32 * q + fk) : zero8;
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[q], acc, 0, 0, 0);
+                    }
                 }
                 if (fk == 0) epilogue(16 * t + fr, acc[0]);  // row 0 of the block: lanes 0-15, component 0
             }
