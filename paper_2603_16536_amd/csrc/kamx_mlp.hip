@@ -299,12 +299,12 @@ __global__ void set_norm_kernel(const float *mu_in, const float *sd_in, int n_in
 // batch of 1000 in four launches of 64-row tiles that waited for memory twice per
 // 32 of K.  Instead a workgroup takes 16 or 32 rows through every layer, and in
 // training back again: activations stay in LDS as BF16 operands, the
-// pre-activations' FP32 values in the registers of the lanes that computed them,
+// activations' derivatives (FP32) in the registers of the lanes that computed them,
 // and weights come from L2 straight into operand registers, four steps of K ahead
 // (eight ahead, or every line touched at the start, gained nothing).  Every sum over
-// K runs in the order of gemm_kernel, so outputs have its bits.  17.5 us for the
-// batch of 1000: 4 standardising, 3 in the first layer's weights, 3.5 in each of the
-// two layers of error functions; a training batch of 4096 takes 34 us.
+// K runs in the order of gemm_kernel, so outputs have its bits.  15.5 us for the
+// batch of 1000 (3 standardising, 4 in the first layer's 360 KB of weights, 2 in each
+// hidden layer's error functions, 3 of launch); a training batch of 4096 takes 31 us.
 
 constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
 constexpr int kRowTiles = 4;  // hidden column tiles a wave keeps, at most
@@ -425,12 +425,21 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
         mine[j] = wave + kRowWaves * j < ht;
         tile[j] = min(wave + kRowWaves * j, ht - 1);
     }
+    // (biases, and below the output layer's scales and targets, ahead of the weights
+    // asked for with them: loads return in order, and an epilogue that loaded its own
+    // waited for all of the next layer's)
+    float b1[TN], b2[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        b1[j] = a.b1[16 * tile[j] + fr];
+        b2[j] = a.b2[16 * tile[j] + fr];
+    }
     Weights<TN> W;
     W.begin(a.w1, a.fp, tile);
 
     // x^ = (x - mu) s in BF16, zero in padded rows and columns: a wave's 2 MB rows
-    // together, four loads of each in flight
-    constexpr int kWaveRows = kRows / kRowWaves, kLoads = 4;
+    // together, six loads of each in flight
+    constexpr int kWaveRows = kRows / kRowWaves, kLoads = 6;
     for (int c0 = lane; c0 < a.fp; c0 += 64 * kLoads) {
         float v[kWaveRows][kLoads], mu[kLoads], sd[kLoads];
 #pragma unroll
@@ -461,21 +470,21 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
             store_k(a.xk, a.fp, m0 + r, c, v);
         }
 
-    // z = act W^T + b; gelu(z) to LDS
-    floatx4 acc[MB][TN], z1[MB][TN], z2[MB][TN];
-    auto hidden = [&](const float *bias, floatx4 (&z)[MB][TN], __bf16 *h, int ld, __bf16 *hk) {
+    // z = act W^T + b; gelu(z) to LDS, and for the way back gelu'(z), which shares its
+    // error function
+    floatx4 acc[MB][TN], d1[MB][TN], d2[MB][TN];
+    auto hidden = [&](const float (&bias)[TN], floatx4 (&dg)[MB][TN], __bf16 *h, int ld, __bf16 *hk) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int n = 16 * tile[j] + fr;
-            const float b = bias[n];
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 bf16x4 o;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const float zv = acc[i][j][c] + b;
-                    z[i][j][c] = zv;
+                    const float zv = acc[i][j][c] + bias[j];
                     o[c] = to_bf16(gelu(zv));
+                    if (TRAIN) dg[i][j][c] = gelu_grad(zv);
                 }
                 if (mine[j]) {
 #pragma unroll
@@ -487,17 +496,31 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
     };
     rows_times<MB, TN>(P, lda, W, acc);
     W.begin(a.w2, H, tile);
-    hidden(a.b1, z1, Q, ldb, a.h1k);
+    hidden(b1, d1, Q, ldb, a.h1k);
     __syncthreads();
     rows_times<MB, TN>(Q, ldb, W, acc);
     int otile[TN];
+    float b3[TN], mu[TN], sd[TN], target[MB][TN][4];
     auto out_tiles = [&](int t0) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) otile[j] = min(t0 + kRowWaves * j, ot - 1);
+        for (int j = 0; j < TN; ++j) {
+            otile[j] = min(t0 + kRowWaves * j, ot - 1);
+            const int n = 16 * otile[j] + fr, nr = min(n, a.n_out - 1);
+            b3[j] = a.b3[n];
+            mu[j] = a.mu_out[nr];
+            sd[j] = a.sd_out[nr];
+            if (TRAIN) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        target[i][j][c] = a.t[min(m0 + 16 * i + rg + c, (long)a.batch - 1) * a.n_out + nr];
+            }
+        }
         W.begin(a.w3, H, otile);
     };
     out_tiles(wave);
-    hidden(a.b2, z2, P, lda, a.h2k);
+    hidden(b2, d2, P, lda, a.h2k);
     __syncthreads();
 
     // outputs, in training their gradients of the mean squared error
@@ -509,20 +532,18 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
         for (int j = 0; j < TN; ++j) {
             if (t0 + kRowWaves * j >= ot) break;
             const int n = 16 * otile[j] + fr;
-            const float b = a.b3[n];
             const bool real = n < a.n_out;
-            const float mu = real ? a.mu_out[n] : 0.f, sd = real ? a.sd_out[n] : 1.f;
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 bf16x4 o;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const long m = m0 + 16 * i + rg + c;
-                    const float yn = acc[i][j][c] + b;
+                    const float yn = acc[i][j][c] + b3[j];
                     if (TRAIN) {
                         float g = 0.f;
                         if (real && m < a.batch) {
-                            const float tn = (a.t[m * a.n_out + n] - mu) / sd;
+                            const float tn = (target[i][j][c] - mu[j]) / sd[j];
                             const float err = yn - tn;
                             sq += err * err;
                             g = 2.f * err / ((float)a.batch * (float)a.n_out);
@@ -531,7 +552,7 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
                         o[c] = to_bf16(g);
                         Q[(16 * i + rg + c) * ldb + n] = o[c];
                     } else if (real && m < a.batch) {
-                        a.y[m * a.ldy + n] = __builtin_fmaf(sd, yn, mu);
+                        a.y[m * a.ldy + n] = __builtin_fmaf(sd[j], yn, mu[j]);
                     }
                 }
                 if (TRAIN) store_k(a.dyk, a.op, m0 + 16 * i + rg, n, o);
@@ -550,7 +571,7 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
     }
 
     // dz = (d W) gelu'(z)
-    auto back = [&](const floatx4 (&z)[MB][TN], __bf16 *d, float *d32, __bf16 *dk) {
+    auto back = [&](const floatx4 (&dg)[MB][TN], __bf16 *d, float *d32, __bf16 *dk) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             if (!mine[j]) break;
@@ -560,7 +581,7 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
                 bf16x4 o;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const float dz = acc[i][j][c] * gelu_grad(z[i][j][c]);
+                    const float dz = acc[i][j][c] * dg[i][j][c];
                     d32[(m0 + 16 * i + rg + c) * H + n] = dz;
                     o[c] = to_bf16(dz);
                     if (d) d[(16 * i + rg + c) * lda + n] = o[c];
@@ -571,10 +592,10 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
     };
     rows_times<MB, TN>(Q, ldb, W, acc);
     W.begin(a.w2t, H, tile);
-    back(z2, P, a.dz2, a.dz2k);
+    back(d2, P, a.dz2, a.dz2k);
     __syncthreads();
     rows_times<MB, TN>(P, lda, W, acc);
-    back(z1, nullptr, a.dz1, a.dz1k);
+    back(d1, nullptr, a.dz1, a.dz1k);
 }
 
 // The gradients of a training step and Adam's update in one launch: 24 us for a
@@ -1016,8 +1037,9 @@ static hipError_t launch_rows_mb(const RowArgs &r, hipStream_t s) {
 
 // A prediction takes 16 rows a workgroup while that is not more than one workgroup per
 // CU, then 32, which halves the weights' traffic: on the biped's network 17.8 us
-// against 20.5 for 4096 rows, but 29.4 against 23.3 for 8192.  (Training keeps two
-// layers' pre-activations in registers and takes 16.)
+// against 20.5 for 4096 rows, but 29.4 against 23.3 for 8192 (before the biases were
+// loaded early).  (Training keeps two
+// layers' derivatives in registers and takes 16.)
 static hipError_t predict_rows(const RowArgs &r, hipStream_t s) {
     return r.R > 16 * kRowLine ? launch_rows_mb<2, false>(r, s) : launch_rows_mb<1, false>(r, s);
 }
