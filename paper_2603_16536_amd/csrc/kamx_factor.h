@@ -81,7 +81,7 @@ __device__ inline void wave_lds_fence() {
 // evenly loaded, and both together pass 2 (T + 1) barriers.  Wave 0's serial
 // diagonal tile bounds a step: its broadcasts are operands of the fused
 // multiply-adds (DPP), one instruction per entry and column.
-// At 224 rows on eight waves: 63 us, against 106 us with the inverse after the
+// At 224 rows on eight waves: 65 us, against 106 us with the inverse after the
 // factorization and the diagonal tile's broadcasts through scalar registers.
 //
 // A: the triangle in LDS, rows m .. the next multiple of 16 identity; Xs:

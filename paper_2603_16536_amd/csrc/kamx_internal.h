@@ -67,14 +67,6 @@ struct SolverParams {
 // from one face to another), the caller's key modulo 512 otherwise.
 __host__ __device__ inline int contact_slot(int key) { return key & (8 * kMaxBodies - 1); }
 
-// Whether iteration it is a checkpoint of the adaptive penalty: first,
-// 2 first, 4 first, ...
-__host__ __device__ inline bool adapt_checkpoint(int it, int first) {
-    if (first <= 0 || it < first || it % first != 0) return false;
-    const int q = it / first;
-    return (q & (q - 1)) == 0;
-}
-
 // A pose advanced by time h with a twist: r + h v, and exp(h [w]x) R by
 // the quaternion exponential (left multiplication, world-frame w),
 // renormalised.  The end-of-step pose update, and (Moreau-Jean) the

@@ -9,12 +9,12 @@
 // and the x-update of Alg. 1 step 5 is a Conjugate Residual solve with a
 // fixed budget, warm-started at the previous iterate (Sec. 4.1, Sec. 5.1).
 //
-// One workgroup per world, one constraint row per thread.  A row's data
+// One workgroup per world, one constraint row per thread.  In the solve a row's data
 // (its J~ 6-blocks, scale, penalty, kind and every ADMM and CR vector entry)
-// stays in the registers of its thread for the whole step; only what other
-// threads read goes through LDS: J~ and the vector being multiplied (read by
-// the body gather), the per-body gather sums (read by the rows) and the
-// per-wave partial sums of the reductions.  A product D~ v costs one body
+// stays in the registers of its thread; only what other threads read goes
+// through LDS: the vector being multiplied and the products of long incidence
+// lists (read by the body gather), the per-body gather sums (read by the rows)
+// and the partial sums of the reductions.  A product D~ v costs one body
 // gather (one thread per body and component, FP64 accumulation over the
 // body's incident rows in increasing row order) and one row evaluation (FP64
 // over the row's two 6-blocks), with a workgroup barrier after each.

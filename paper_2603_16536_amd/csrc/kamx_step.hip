@@ -3,8 +3,9 @@
 // Everything a world needs -- body state, joint frames, contact rows, the
 // preconditioned Delassus matrix, its factor and the ADMM vectors -- lives in
 // LDS for the whole step, so HBM sees only the per-world inputs and outputs.
-// Thread i owns constraint row i (and the block that starts at row i: one
-// row for joints and limits, three rows for a contact).
+// While the rows are built, thread i owns constraint row i (and the block that
+// starts at row i: one row for joints and limits, three rows for a contact); the
+// solve gives row i to the lane pair 2 i, 2 i + 1.
 //
 // Steps (Tsounis et al. 2026):
 //   bodies: R(q), M^-1 applied in the body frame, Newton-Euler forces with
@@ -235,12 +236,6 @@ __device__ inline void reduce_max_sum(float &m, float &s, float *red) {
     }
     m = uniform(m);
     s = uniform(s);
-}
-
-__device__ inline float dot4(const float *a, const float *b) {
-    float4 x = *reinterpret_cast<const float4 *>(a);
-    float4 y = *reinterpret_cast<const float4 *>(b);
-    return x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
 }
 
 // Workgroup sizes each dense row bucket is built for (the first is the
@@ -1644,11 +1639,8 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
     // ---- warm start (Alg. 1 step 2; Sec. 4.1): y = x = Pi_K(lambda_ws / p),
     //      z = v~(y) + Gamma(v~(y)) on unilateral rows, 0 on bilateral rows
     float *vx = L.vec(VX), *vyh = L.vec(VYH), *vzh = L.vec(VZH), *vyp = L.vec(VYP), *vzp = L.vec(VZP);
-    float *vrhs = L.vec(VRHS), *vxn = L.vec(VXN), *vws = L.vec(VWS), *vaux = L.vec(VAUX);
+    float *vws = L.vec(VWS), *vaux = L.vec(VAUX);
     float *vrinv = L.vec(VCOL), *vdx = L.vec(VDX);  // vrinv: 1/rho per row inside the iteration loop
-    // p x per row in FP64 inside the iteration loop, over the warm-start and aux fields
-    double *px = reinterpret_cast<double *>(vws);
-    static_assert(VAUX == VWS + 1 && (VWS * MC) % 2 == 0, "MC doubles in two adjacent fields");
     const int wmode = reset ? KAMX_WARM_COLD : P.warmstart;
     const int kind_i = i < m ? L.ri(RKIND, i) : -1;
     const bool owner = i < m && kind_i != kRowTangent;
