@@ -1011,14 +1011,11 @@ static RowArgs row_args(kamx_mlp n, const float *x, long ldx, int batch) {
 template <int MB, int TN, bool TRAIN>
 static hipError_t launch_rows_tn(const RowArgs &r, hipStream_t s) {
     const size_t lds = row_lds_bytes(r.fp, r.H, r.op, MB, TRAIN);
-    if (MB > 1) {
-        static bool configured = false;
-        if (!configured) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rows_kernel<MB, TN, TRAIN>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)(MB * kRowLds));
-            if (e != hipSuccess) return e;
-            configured = true;
-        }
+    if (lds > kRowLds) {
+        // (on every call: the attribute belongs to the current device)
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rows_kernel<MB, TN, TRAIN>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((rows_kernel<MB, TN, TRAIN>), dim3((unsigned)(r.R / (16 * MB))), dim3(kRowThreads), lds, s, r);
     return hipGetLastError();

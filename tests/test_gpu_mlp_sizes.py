@@ -60,13 +60,15 @@ def test_network_sizes(n_in, n_hidden, n_out, batch):
     d.close()
 
 
-def test_rows_do_not_depend_on_the_batch():
-    """Workgroups of 32 rows (large batches) and of 16 give a row the same bits."""
+@pytest.mark.parametrize("n_in,n_hidden", [(130, 128), (1300, 256)])
+def test_rows_do_not_depend_on_the_batch(n_in, n_hidden):
+    """Workgroups of 32 rows (large batches; past 64 KB of LDS for the wider network)
+    and of 16 give a row the same bits."""
     rng = np.random.default_rng(5)
-    net = random_net(rng, 130, 128, 70)
+    net = random_net(rng, n_in, n_hidden, 70)
     n = 20000
     d = device_net(net, n)
-    x = torch.as_tensor(rng.normal(0, 2, (n, 130)).astype(np.float32), device="cuda")
+    x = torch.as_tensor(rng.normal(0, 2, (n, n_in)).astype(np.float32), device="cuda")
     y = d.forward(x)
     for lo, hi in ((0, 1000), (9999, 11000), (n - 17, n)):
         assert torch.equal(y[lo:hi], d.forward(x[lo:hi].contiguous()))
