@@ -184,6 +184,20 @@ struct StepArgs {
     int32_t n_contact_slots;     // contact keys with a slot (probes per world, else contact capacity)
 };
 
+// Workgroup sizes each dense row bucket is built for (the first is the
+// default; see step_threads_variants).
+struct BucketSizes {
+    int mc, n, nt[3];
+};
+constexpr BucketSizes kBucketSizes[] = {{32, 3, {256, 128, 64}}, {64, 2, {256, 128, 0}}, {96, 2, {512, 256, 0}},
+                                        {128, 2, {512, 256, 0}}, {160, 2, {384, 512, 0}}, {192, 2, {384, 512, 0}},
+                                        {224, 1, {512, 0, 0}}};
+
+// Row groups of four g and Q - 1 - g of a world's Q <= mc / 4 form pair g of the passes
+// over the triangle, 16 threads to a pair: g < mc / 8.  The pair whose rows thread
+// group gg reads; those past the last pair get its rows.
+__host__ __device__ constexpr int pair_first(int gg, int mc) { return gg < mc / 8 - 1 ? gg : mc / 8 - 1; }
+
 // Packed lower-triangular storage with every row padded to a multiple of 4
 // floats (so rows can be read as float4): offset of row i.
 // (i < 256; the masks tell the compiler that a 24-bit multiply will do)

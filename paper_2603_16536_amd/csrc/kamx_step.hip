@@ -238,15 +238,6 @@ __device__ inline void reduce_max_sum(float &m, float &s, float *red) {
     s = uniform(s);
 }
 
-// Workgroup sizes each dense row bucket is built for (the first is the
-// default; see step_threads_variants).
-struct BucketSizes {
-    int mc, n, nt[3];
-};
-constexpr BucketSizes kBucketSizes[] = {{32, 3, {256, 128, 64}}, {64, 2, {256, 128, 0}}, {96, 2, {512, 256, 0}},
-                                        {128, 2, {512, 256, 0}}, {160, 2, {384, 512, 0}}, {192, 2, {384, 512, 0}},
-                                        {224, 1, {512, 0, 0}}};
-
 // The default workgroup size of a bucket.  The gather's four-thread bodies
 // are capped by it rather than by the launched size, so that every size of a
 // bucket sums each body in the same order (a smaller size runs the gather's
@@ -796,12 +787,15 @@ __device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int
         // the pads of the diagonal quad hold 0 and r is 0 past row m, and rows
         // past m (up to the next multiple of 16) hold finite values whose sums are
         // not stored.  Two quads' reads are in flight at a time; a lane past its
-        // group's last quad reads that quad against zeros.
+        // group's last quad reads that quad against zeros, and threads past the
+        // last pair read the last one's rows (96 rows on 512 threads have 32 thread
+        // groups for 12 pairs) for sums that are not stored either.
         {
             int to = tid;
             asm volatile("" : "+v"(to));  // addresses formed here, not held through the loop
             const int gg = to >> 4, kk = to & 15;
-            const int G1 = gg, G2 = max(Q - 1 - gg, 0);
+            const int G1 = pair_first(gg, MC), G2 = max(Q - 1 - gg, 0);
+            static_assert(4 * pair_first(NT / 16 - 1, MC) + 3 < MC, "the t pass stays in the triangle");
             const float *R1 = A + tri_row_offset(4 * G1), *R2 = A + tri_row_offset(4 * G2);
             mfx4 s1 = kZero4, s2 = kZero4;
             struct Chunk {
