@@ -87,7 +87,7 @@ __device__ inline void wave_lds_fence() {
 // A: the triangle in LDS, rows m .. the next multiple of 16 identity; Xs:
 // kFactorScratch floats of LDS (the 16x16 inverse of the current diagonal factor
 // tile, rows 17 apart for the LDS banks, and a spare place); flag: an int in LDS.
-// m <= MC rows, uniform; every thread of the workgroup calls.
+// 0 <= m <= MC rows, uniform; every thread of the workgroup calls.
 constexpr int kFactorScratch = 288 + 64;
 
 template <int MC, int NT>
@@ -215,6 +215,7 @@ __device__ __forceinline__ int factor_invert_tiles(float *A, float *Xs, int *fla
     };
     if (tid == 0) *flag = 0;
     __syncthreads();
+    if (T == 0) return 0;  // no rows: nothing has written the triangle
     if (wv == 0) factor_diag(0);
     __syncthreads();
     for (int K = 0; K <= T; ++K) {
