@@ -501,7 +501,8 @@ kamx_status kamx_mlp_info(kamx_mlp net, int32_t *n_in_pad, int32_t *n_out_pad, i
 kamx_status kamx_mlp_set_normalization(kamx_mlp net, const float *mu_in, const float *sigma_in, const float *mu_out,
                                        const float *sigma_out, kamx_stream stream);
 
-/* y_dev [batch][n_out] = network(x_dev [batch][n_in]); 1 <= batch <= max_batch. */
+/* y_dev [batch][n_out] = network(x_dev [batch][n_in]); 1 <= batch <= max_batch.
+ * y_dev may share memory with x_dev: all of x counts as read before y is written. */
 kamx_status kamx_mlp_forward(kamx_mlp net, const float *x_dev, int32_t batch, float *y_dev, kamx_stream stream);
 
 /* The forward pass of kamx_mlp_forward for callers that cannot allocate

@@ -1111,7 +1111,12 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
                                     long ldy, hipStream_t s) {
     const int R = pad64(batch), H = n->H, fp = n->fp, op = n->op;
     const Layout &L = n->L;
-    if (n->fused && !a.z1) {
+    // the row kernel writes a workgroup's outputs while others still read their inputs;
+    // one product per layer reads all of x first, and its outputs have the same bits
+    const uintptr_t x0 = (uintptr_t)x, x1 = (uintptr_t)(x + (batch - 1) * ldx + n->n_in);
+    const uintptr_t y0 = (uintptr_t)y, y1 = (uintptr_t)(y + (batch - 1) * ldy + n->n_out);
+    const bool overlap = y0 < x1 && x0 < y1;
+    if (n->fused && !a.z1 && !overlap) {
         RowArgs r = row_args(n, x, ldx, batch);
         r.y = y;
         r.ldy = ldy;
