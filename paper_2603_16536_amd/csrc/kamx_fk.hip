@@ -271,14 +271,9 @@ hipError_t launch_fk(const WorldInfo *worlds, int n_worlds, const int32_t *jint,
                      const float *inertia, float *q, float *u, const float *targets, int max_iters, float tol,
                      int32_t *iters, float *resid, hipStream_t stream) {
     if (n_worlds <= 0) return hipSuccess;
-    static bool configured = false;
     const size_t bytes = fk_smem_bytes();
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)fk_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)bytes);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    hipError_t e = allow_lds((const void *)fk_kernel, bytes);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fk_kernel, dim3(n_worlds), dim3(kFkThreads), bytes, stream, worlds, jint, jf, mass, inertia, q,
                        u, targets, max_iters, tol, iters, resid);
     return hipGetLastError();

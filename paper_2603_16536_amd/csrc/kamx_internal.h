@@ -184,6 +184,15 @@ struct StepArgs {
     int32_t n_contact_slots;     // contact keys with a slot (probes per world, else contact capacity)
 };
 
+// Dynamic LDS a kernel takes as it is (64 KB, some of it left to static variables).
+// More is allowed by an attribute, which belongs to the current device and is
+// therefore set on every call.
+constexpr size_t kPlainLds = 65536 - 64;
+inline hipError_t allow_lds(const void *kernel, size_t bytes) {
+    if (bytes <= kPlainLds) return hipSuccess;
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 // Workgroup sizes each dense row bucket is built for (the first is the
 // default; see step_threads_variants).
 struct BucketSizes {

@@ -310,7 +310,6 @@ constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
 constexpr int kRowTiles = 4;  // hidden column tiles a wave keeps, at most
 constexpr int kAhead = 4;     // steps of K loaded ahead
 constexpr int kRowLine = 256;  // workgroups of 16 rows, at most
-constexpr size_t kRowLds = 65536 - 64;  // of dynamic LDS, besides the static partial sums
 
 struct RowArgs {
     const float *x;
@@ -339,7 +338,7 @@ inline size_t row_lds_bytes(int fp, int H, int op, int mb, bool train) {
 // Networks whose rows fit 64 KB of LDS and whose hidden columns fit the registers;
 // wider ones go through one product per layer.
 inline bool rows_kernel_takes(int fp, int H, int op) {
-    return H <= 16 * kRowTiles * kRowWaves && row_lds_bytes(fp, H, op, 1, true) <= kRowLds;
+    return H <= 16 * kRowTiles * kRowWaves && row_lds_bytes(fp, H, op, 1, true) <= kPlainLds;
 }
 
 // Weights of up to TN column tiles on their way from L2: kAhead steps of K.  The first
@@ -1011,12 +1010,8 @@ static RowArgs row_args(kamx_mlp n, const float *x, long ldx, int batch) {
 template <int MB, int TN, bool TRAIN>
 static hipError_t launch_rows_tn(const RowArgs &r, hipStream_t s) {
     const size_t lds = row_lds_bytes(r.fp, r.H, r.op, MB, TRAIN);
-    if (lds > kRowLds) {
-        // (on every call: the attribute belongs to the current device)
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rows_kernel<MB, TN, TRAIN>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
+    hipError_t e = allow_lds(reinterpret_cast<const void *>(&rows_kernel<MB, TN, TRAIN>), lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((rows_kernel<MB, TN, TRAIN>), dim3((unsigned)(r.R / (16 * MB))), dim3(kRowThreads), lds, s, r);
     return hipGetLastError();
 }

@@ -1122,14 +1122,9 @@ template <int NT>
 static hipError_t launch_sparse(const StepArgs &args, int n, hipStream_t stream) {
     static_assert(NT % 64 == 0 && NT >= 64 && NT <= 1024, "unsupported workgroup size");
     const size_t smem = sizeof(float) * (size_t)sp_smem_floats(NT);
-    static bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sparse_step_kernel<NT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
     if (n <= 0) return hipSuccess;
+    hipError_t e = allow_lds(reinterpret_cast<const void *>(&sparse_step_kernel<NT>), smem);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sparse_step_kernel<NT>, dim3(n), dim3(NT), smem, stream, args);
     return hipGetLastError();
 }

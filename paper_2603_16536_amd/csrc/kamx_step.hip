@@ -1937,13 +1937,8 @@ template <int MC, int NT>
 static hipError_t launch_mc(const StepArgs &args, int n, hipStream_t stream) {
     static_assert(NT % 64 == 0 && NT >= 64 && NT >= 2 * MC && NT <= 512, "unsupported workgroup size");
     size_t bytes = sizeof(float) * (size_t)smem_floats(MC);
-    static bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)step_kernel<MC, NT>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    hipError_t e = allow_lds((const void *)step_kernel<MC, NT>, bytes);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((step_kernel<MC, NT>), dim3(n), dim3(NT), bytes, stream, args);
     return hipGetLastError();
 }
