@@ -1081,8 +1081,8 @@ static hipError_t train_fused(kamx_mlp n, const float *x, const float *target, i
     g.m = n->am;
     g.v = n->av;
     g.lr = lr;
-    g.c1 = (float)(1.0 - pow(0.9, n->t));
-    g.c2 = (float)(1.0 - pow(0.999, n->t));
+    g.c1 = (float)(1.0 - pow(0.9, n->t + 1));
+    g.c2 = (float)(1.0 - pow(0.999, n->t + 1));
     g.loss_scale = 1.f / ((float)batch * (float)n->n_out);
     g.loss_part = n->ws;
     g.loss = loss;
@@ -1257,8 +1257,8 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     const int R = pad64(batch), H = n->H, fp = n->fp, op = n->op;
     const Layout &L = n->L;
     if (n->fused) {
-        n->t += 1;
         MLP_HIP(train_fused(n, x, y_target, batch, lr, loss_dev, s));
+        n->t += 1;
         return KAMX_OK;
     }
     kamx_status st = mlp_forward_rows(n, own_acts(n, true), x, n->n_in, batch, nullptr, 0, s);
@@ -1296,11 +1296,11 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     MLP_HIP(gemm_store(n, Operand{n->dz1b, 1, H}, Operand{n->xh, 1, fp}, H, fp, R, n->g + L.oW1, s));
     MLP_HIP(colsum(n, n->dz1, R, H, n->g + L.ob1, s));
     // Adam
-    n->t += 1;
-    const float c1 = (float)(1.0 - pow(0.9, n->t)), c2 = (float)(1.0 - pow(0.999, n->t));
+    const float c1 = (float)(1.0 - pow(0.9, n->t + 1)), c2 = (float)(1.0 - pow(0.999, n->t + 1));
     hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((L.total + 255) / 256)), dim3(256), 0, s, n->w, n->g, n->am,
                        n->av, L.total, lr, c1, c2, L, n->wb);
     MLP_HIP(hipGetLastError());
+    n->t += 1;
     return KAMX_OK;
 }
 

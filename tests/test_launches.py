@@ -75,3 +75,65 @@ def test_large_lds_on_every_device(tmp_path):
     raised for it on the device that is current, also when another device used it
     first."""
     run(tmp_path, DEVICES)
+
+
+ADAM = r"""
+#include <cmath>
+#include "fake_hip.h"
+#include "kamx.h"
+static int count, fail_at = -1;
+static float c1, c2;
+static const float kLr = 0.12345f;
+// the bias corrections of the update: beside the learning rate in the arguments
+static void seen(const fake::Launch &l) {
+    if (l.name.find("adam_kernel") != std::string::npos) {
+        c1 = *(float *)l.args[6];
+        c2 = *(float *)l.args[7];
+    } else if (l.name.find("grads_kernel") != std::string::npos) {
+        float v[48];
+        std::memcpy(v, l.args[0], sizeof(v));
+        for (int k = 0; k + 2 < 48; ++k)
+            if (v[k] == kLr) {
+                c1 = v[k + 1];
+                c2 = v[k + 2];
+            }
+    }
+}
+static bool failing(const std::string &) { return count++ == fail_at; }
+int main() {
+    fake::on_launch = seen;
+    fake::fail_launch = failing;
+    for (int hidden : {64, 576}) {
+        kamx_mlp n;
+        std::vector<float> x(64 * 10), y(64 * 10);
+        float loss;
+        if (kamx_mlp_create(10, hidden, 10, 64, 1, &n) != KAMX_OK) return 1;
+        int good = 0, failed = 0;
+        for (int k = 0; k < 40; ++k) {
+            // every launch of a step fails in one of the odd calls
+            fail_at = k % 2 ? k / 2 : -1;
+            count = 0;
+            c1 = c2 = 0.f;
+            const bool ok = kamx_mlp_train_step(n, x.data(), y.data(), 64, kLr, &loss, nullptr) == KAMX_OK;
+            if (!ok) {
+                ++failed;
+                continue;
+            }
+            ++good;
+            const float w1 = (float)(1.0 - std::pow(0.9, good)), w2 = (float)(1.0 - std::pow(0.999, good));
+            if (c1 != w1 || c2 != w2) {
+                std::printf("%d hidden, %d updates, %d failed: corrections %g %g, not %g %g\n", hidden, good, failed, c1, c2, w1, w2);
+                return 1;
+            }
+        }
+        std::printf("%d hidden: %d updates, %d failed\n", hidden, good, failed);
+        if (failed < 2) return 1;
+    }
+    return 0;
+}
+"""
+
+
+def test_failed_training_steps_do_not_count(tmp_path):
+    """Adam's bias corrections count the updates that were launched."""
+    run(tmp_path, ADAM)
