@@ -119,13 +119,14 @@ __host__ __device__ inline long weight_at(int row, int col, int cols) {
     return ((long)(row >> 4) * (cols >> 5) + (col >> 5)) * 512 + (row & 15) * 32 + (col & 31);
 }
 
-// Device view of a network's parameters (BF16 weights [out][in_pad] in the order
-// of weight_at, FP32 biases and standardisation).
+// Device view of a network's parameters (BF16 weights [out][in_pad], in the order
+// of weight_at or row-major, FP32 biases and standardisation).
 struct MlpView {
     const __bf16 *w1, *w2, *w3;
     const float *b1, *b2, *b3;
     const float *mu_in, *s_in, *mu_out, *sd_out;
     int32_t n_in, fp, H, n_out, op;
+    int32_t blocked;  // weights in the order of weight_at
 };
 
 struct StepArgs {

@@ -38,16 +38,10 @@ inline int grad_splits(int M, int N, int K) {
 }
 
 
-// element (i, k) of an operand at p[i * si + k * sk], one of the strides 1; or of a
-// weight matrix of cols columns, its rows along i (sk = 1) or along k
+// element (i, k) of an operand at p[i * si + k * sk]; one of the strides is 1
 struct Operand {
     const __bf16 *p;
     long si, sk;
-    int cols = 0;
-    // where eight elements start that lie side by side: rows r, columns c .. c + 7
-    __device__ const __bf16 *at(long r, long c, long ld) const {
-        return p + (cols ? weight_at((int)r, (int)c, cols) : r * ld + c);
-    }
 };
 
 enum Epilogue { kEpiHidden = 0, kEpiOut = 1, kEpiBackward = 2, kEpiStore = 3 };
@@ -72,11 +66,11 @@ __device__ inline void stage(const Operand &o, long i0, long k0, __bf16 *tile) {
     const int t = threadIdx.x;
     if (o.sk == 1) {
         const int r = t >> 2, kc = (t & 3) * 8;
-        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.at(i0 + r, k0 + kc, o.si));
+        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.p + (i0 + r) * o.si + k0 + kc);
         *reinterpret_cast<bf16x8 *>(tile + r * kLdsRow + kc) = v;
     } else {
         const int k = t >> 3, ic = (t & 7) * 8;
-        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.at(k0 + k, i0 + ic, o.sk));
+        bf16x8 v = *reinterpret_cast<const bf16x8 *>(o.p + (k0 + k) * o.sk + i0 + ic);
 #pragma unroll
         for (int j = 0; j < 8; ++j) tile[(ic + j) * kLdsRow + k] = v[j];
     }
@@ -221,6 +215,10 @@ __global__ void sum_slices_kernel(const float *part, long stride, int ns, long n
     out[i] = t;
 }
 
+// A network of the row kernel keeps its BF16 weights in the order of weight_at, those of
+// the second and third layer transposed as well; one of a product per layer keeps
+// them row-major, whose 128-byte lines serve a tile of 32 columns and the next (in the
+// other order a thousand rows of 667-576-224 took 64 us instead of 53).
 struct Layout {
     long oW1, ob1, oW2, ob2, oW3, ob3, total;  // packed FP32 parameters
     long bW1, bW2, bW3, btotal;                // BF16 weight copies
@@ -228,26 +226,26 @@ struct Layout {
     int fp, H, op;
 };
 
-// The BF16 copies of element (r, c) of layer p's weights.
+// The BF16 copies of element (r, c) of layer p's weights in a network of the row kernel.
 __device__ inline void store_weight(const Layout &L, int p, int r, int c, float wi, __bf16 *wb) {
     const __bf16 v = to_bf16(wi);
     if (p == 0) {
         wb[L.bW1 + weight_at(r, c, L.fp)] = v;
     } else if (p == 1) {
         wb[L.bW2 + weight_at(r, c, L.H)] = v;
-        if (L.bT2) wb[L.bT2 + weight_at(c, r, L.H)] = v;
+        wb[L.bT2 + weight_at(c, r, L.H)] = v;
     } else {
         wb[L.bW3 + weight_at(r, c, L.H)] = v;
-        if (L.bT3) wb[L.bT3 + weight_at(c, r, L.op)] = v;
+        wb[L.bT3 + weight_at(c, r, L.op)] = v;
     }
 }
 
-// The same for parameter i, where it is a weight.
-__device__ inline void store_bf16(const Layout &L, long i, float wi, __bf16 *wb) {
-    const int p = i >= L.oW3 ? 2 : (i >= L.oW2 ? 1 : 0);
-    const long k = i - (p == 2 ? L.oW3 : (p == 1 ? L.oW2 : L.oW1));
-    const int cols = p ? L.H : L.fp, r = (int)(k / cols);
-    if (r < (p == 2 ? L.op : L.H)) store_weight(L, p, r, (int)(k - (long)r * cols), wi, wb);
+// Where the BF16 copy of parameter i lies in a network of a product per layer (-1: a bias).
+__device__ inline long row_major_at(const Layout &L, long i) {
+    if (i >= L.oW1 && i < L.ob1) return L.bW1 + (i - L.oW1);
+    if (i >= L.oW2 && i < L.ob2) return L.bW2 + (i - L.oW2);
+    if (i >= L.oW3 && i < L.ob3) return L.bW3 + (i - L.oW3);
+    return -1;
 }
 
 // One bias-corrected Adam update of parameter i by its gradient.
@@ -262,18 +260,29 @@ __device__ inline float adam_update(float *w, float *m, float *v, long i, float 
 }
 
 // Bias-corrected Adam on the packed FP32 parameters; weights also refresh
-// their BF16 copies.
+// their BF16 copies (networks of a product per layer).
 __global__ void adam_kernel(float *w, const float *g, float *m, float *v, long n, float lr, float c1, float c2,
                             Layout L, __bf16 *wb) {
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    store_bf16(L, i, adam_update(w, m, v, i, g[i], lr, c1, c2), wb);
+    const float wi = adam_update(w, m, v, i, g[i], lr, c1, c2);
+    const long bi = row_major_at(L, i);
+    if (bi >= 0) wb[bi] = to_bf16(wi);
 }
 
 __global__ void refresh_bf16_kernel(const float *w, Layout L, __bf16 *wb) {
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= L.total) return;
-    store_bf16(L, i, w[i], wb);
+    const long bi = row_major_at(L, i);
+    if (bi < 0) return;
+    if (!L.bT2) {
+        wb[bi] = to_bf16(w[i]);
+        return;
+    }
+    const int p = i >= L.oW3 ? 2 : (i >= L.oW2 ? 1 : 0), cols = p ? L.H : L.fp;
+    const long k = i - (p == 2 ? L.oW3 : (p == 1 ? L.oW2 : L.oW1));
+    const int r = (int)(k / cols);
+    store_weight(L, p, r, (int)(k - (long)r * cols), w[i], wb);
 }
 
 // s = 1 / sigma (0 for constant features); sigma_out floored at 1e-12 -> 1.
@@ -324,6 +333,7 @@ struct RowArgs {
     // gradients ([R / 32][columns][32 rows]), the gradients' FP32 values [R][columns]
     // for the bias gradients, and the squared error per workgroup
     const float *t;
+    const __bf16 *xh;  // prediction: the standardised input [R][fp] in x's place, or null
     __bf16 *xk, *h1k, *h2k, *dyk, *dz2k, *dz1k;
     float *dy, *dz2, *dz1, *loss_part;
 };
@@ -439,7 +449,13 @@ __global__ __launch_bounds__(kRowThreads) void rows_kernel(RowArgs a) {
     // x^ = (x - mu) s in BF16, zero in padded rows and columns: a wave's 2 MB rows
     // together, six loads of each in flight
     constexpr int kWaveRows = kRows / kRowWaves, kLoads = 6;
-    for (int c0 = lane; c0 < a.fp; c0 += 64 * kLoads) {
+    const bool given = !TRAIN && a.xh;
+    if (given)
+        for (int i = threadIdx.x; i < kRows * (a.fp / 8); i += kRowThreads) {
+            const int r = i / (a.fp / 8), c = 8 * (i - r * (a.fp / 8));
+            *reinterpret_cast<bf16x8 *>(P + r * lda + c) = *reinterpret_cast<const bf16x8 *>(a.xh + (m0 + r) * a.fp + c);
+        }
+    for (int c0 = given ? a.fp : lane; c0 < a.fp; c0 += 64 * kLoads) {
         float v[kWaveRows][kLoads], mu[kLoads], sd[kLoads];
 #pragma unroll
         for (int e = 0; e < kLoads; ++e) {
@@ -1106,32 +1122,37 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
                                     long ldy, hipStream_t s) {
     const int R = pad64(batch), H = n->H, fp = n->fp, op = n->op;
     const Layout &L = n->L;
-    // the row kernel writes a workgroup's outputs while others still read their inputs;
-    // one product per layer reads all of x first, and its outputs have the same bits
+    const bool rows = n->fused && !a.z1;
+    // the row kernel writes a workgroup's outputs while others still read their inputs, so
+    // outputs over their inputs (the arrays share memory) have the inputs standardised
+    // by a launch of their own
     const uintptr_t x0 = (uintptr_t)x, x1 = (uintptr_t)(x + (batch - 1) * ldx + n->n_in);
     const uintptr_t y0 = (uintptr_t)y, y1 = (uintptr_t)(y + (batch - 1) * ldy + n->n_out);
     const bool overlap = y0 < x1 && x0 < y1;
-    if (n->fused && !a.z1 && !overlap) {
+    if (!rows || overlap) {
+        const long cnt = (long)R * fp;
+        hipLaunchKernelGGL(normalise_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, x, ldx, batch,
+                           n->n_in, n->mu_in, n->s_in, a.xh, R, fp);
+        MLP_HIP(hipGetLastError());
+    }
+    if (rows) {
         RowArgs r = row_args(n, x, ldx, batch);
+        r.xh = overlap ? a.xh : nullptr;
         r.y = y;
         r.ldy = ldy;
         MLP_HIP(predict_rows(r, s));
         return KAMX_OK;
     }
-    long cnt = (long)R * fp;
-    hipLaunchKernelGGL(normalise_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, x, ldx, batch, n->n_in,
-                       n->mu_in, n->s_in, a.xh, R, fp);
-    MLP_HIP(hipGetLastError());
     EpiArgs e{};
     e.bias = n->w + L.ob1;
     e.f32 = a.z1;
     e.b16 = a.h1;
     e.ld = H;
-    MLP_HIP((gemm<kEpiHidden>(Operand{a.xh, fp, 1}, Operand{n->wb + L.bW1, fp, 1, fp}, R, H, fp, e, s)));
+    MLP_HIP((gemm<kEpiHidden>(Operand{a.xh, fp, 1}, Operand{n->wb + L.bW1, fp, 1}, R, H, fp, e, s)));
     e.bias = n->w + L.ob2;
     e.f32 = a.z2;
     e.b16 = a.h2;
-    MLP_HIP((gemm<kEpiHidden>(Operand{a.h1, H, 1}, Operand{n->wb + L.bW2, H, 1, H}, R, H, H, e, s)));
+    MLP_HIP((gemm<kEpiHidden>(Operand{a.h1, H, 1}, Operand{n->wb + L.bW2, H, 1}, R, H, H, e, s)));
     EpiArgs o{};
     o.bias = n->w + L.ob3;
     o.f32 = a.yn;
@@ -1142,7 +1163,7 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
     o.n_out = n->n_out;
     o.mu = n->mu_out;
     o.sigma = n->sd_out;
-    MLP_HIP((gemm<kEpiOut>(Operand{a.h2, H, 1}, Operand{n->wb + L.bW3, H, 1, H}, R, op, H, o, s)));
+    MLP_HIP((gemm<kEpiOut>(Operand{a.h2, H, 1}, Operand{n->wb + L.bW3, H, 1}, R, op, H, o, s)));
     return KAMX_OK;
 }
 
@@ -1180,6 +1201,7 @@ MlpView mlp_view(kamx_mlp n) {
     v.H = n->H;
     v.n_out = n->n_out;
     v.op = n->op;
+    v.blocked = n->fused;
     return v;
 }
 int mlp_n_out(kamx_mlp n) { return n->n_out; }
@@ -1282,7 +1304,7 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     e.f32 = n->dz2;
     e.b16 = n->dz2b;
     e.ld = H;
-    MLP_HIP((gemm<kEpiBackward>(Operand{n->dyb, op, 1}, Operand{n->wb + L.bW3, 1, H, H}, R, H, op, e, s)));
+    MLP_HIP((gemm<kEpiBackward>(Operand{n->dyb, op, 1}, Operand{n->wb + L.bW3, 1, H}, R, H, op, e, s)));
     // layer 2
     MLP_HIP(gemm_store(n, Operand{n->dz2b, 1, H}, Operand{n->h1, 1, H}, H, H, R, n->g + L.oW2, s));
     MLP_HIP(colsum(n, n->dz2, R, H, n->g + L.ob2, s));
@@ -1291,7 +1313,7 @@ extern "C" kamx_status kamx_mlp_train_step(kamx_mlp n, const float *x, const flo
     e.f32 = n->dz1;
     e.b16 = n->dz1b;
     e.ld = H;
-    MLP_HIP((gemm<kEpiBackward>(Operand{n->dz2b, H, 1}, Operand{n->wb + L.bW2, 1, H, H}, R, H, H, e, s)));
+    MLP_HIP((gemm<kEpiBackward>(Operand{n->dz2b, H, 1}, Operand{n->wb + L.bW2, 1, H}, R, H, H, e, s)));
     // layer 1
     MLP_HIP(gemm_store(n, Operand{n->dz1b, 1, H}, Operand{n->xh, 1, fp}, H, fp, R, n->g + L.oW1, s));
     MLP_HIP(colsum(n, n->dz1, R, H, n->g + L.ob1, s));

@@ -1233,13 +1233,14 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
         auto layer = [&](const __bf16 *x, int K, const __bf16 *Wt, int nout_pad, auto &&epilogue) {
             for (int t = wv; t < nout_pad / 16; t += NW) {
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                const __bf16 *wt = Wt + (long)t * (K >> 5) * 512 + fr * 32 + fk;
+                const __bf16 *wt = Wt + (long)t * 16 * K + fr * (N.blocked ? 32 : K) + fk;
+                const int step32 = N.blocked ? 512 : 32;  // from 32 columns to the next
                 constexpr int kAhead = 8;  // steps of K loaded together
                 for (int k0 = 0; k0 < K; k0 += 32 * kAhead) {
                     bf16x8 bv[kAhead];
 #pragma unroll
                     for (int q = 0; q < kAhead; ++q)
-                        bv[q] = *reinterpret_cast<const bf16x8 *>(wt + (min(k0 + 32 * q, K - 32) >> 5) * 512);
+                        bv[q] = *reinterpret_cast<const bf16x8 *>(wt + (min(k0 + 32 * q, K - 32) >> 5) * step32);
 #pragma unroll
                     for (int q = 0; q < kAhead; ++q) {
                         if (k0 + 32 * q >= K) break;
