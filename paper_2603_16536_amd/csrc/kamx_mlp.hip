@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "kamx_internal.h"
@@ -76,10 +77,17 @@ __device__ inline void stage(const Operand &o, long i0, long k0, __bf16 *tile) {
     }
 }
 
+// The same from a weight matrix of K columns in the order of weight_at.
+__device__ inline void stage_blocked(const __bf16 *W, int K, long n0, long k0, __bf16 *tile) {
+    const int t = threadIdx.x, r = t >> 2, kc = (t & 3) * 8;
+    const bf16x8 v = *reinterpret_cast<const bf16x8 *>(W + weight_at((int)n0 + r, kc, K) + k0 * 16);
+    *reinterpret_cast<bf16x8 *>(tile + r * kLdsRow + kc) = v;
+}
+
 // C[M, N] = sum_k A(m, k) B(n, k), M, N multiples of 64 and K of 32 (the
 // host pads every dimension).  Four waves, each a 32 x 32 quarter of the
-// tile as 2 x 2 matrix-core blocks of 16 x 16.
-template <int EPI>
+// tile as 2 x 2 matrix-core blocks of 16 x 16.  BLOCKED: B in the order of weight_at.
+template <int EPI, bool BLOCKED = false>
 __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(Operand A, Operand B, int M, int N, int K, EpiArgs e) {
     __shared__ __attribute__((aligned(16))) __bf16 As[kTileM * kLdsRow];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[kTileN * kLdsRow];
@@ -97,7 +105,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(Operand A, Operand B
     for (int k0 = kb; k0 < kb + kspan; k0 += kTileK) {
         __syncthreads();
         stage(A, m0, k0, As);
-        stage(B, n0, k0, Bs);
+        if (BLOCKED) stage_blocked(B.p, K, n0, k0, Bs);
+        else stage(B, n0, k0, Bs);
         __syncthreads();
         bf16x8 a[2], b[2];
 #pragma unroll
@@ -956,10 +965,10 @@ extern "C" kamx_status kamx_mlp_set_normalization(kamx_mlp n, const float *mu_in
     return KAMX_OK;
 }
 
-template <int EPI>
+template <int EPI, bool BLOCKED = false>
 static hipError_t gemm(const Operand &A, const Operand &B, int M, int N, int K, const EpiArgs &e, hipStream_t s) {
     if (M % kTileM || N % kTileN || K % kTileK || M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gemm_kernel<EPI>, dim3(N / kTileN, M / kTileM), dim3(kGemmThreads), 0, s, A, B, M, N, K, e);
+    hipLaunchKernelGGL((gemm_kernel<EPI, BLOCKED>), dim3(N / kTileN, M / kTileM), dim3(kGemmThreads), 0, s, A, B, M, N, K, e);
     return hipGetLastError();
 }
 
@@ -1108,6 +1117,20 @@ static hipError_t train_fused(kamx_mlp n, const float *x, const float *target, i
     return hipGetLastError();
 }
 
+// Where one product per layer predicts faster than the row kernel although the network
+// fits it: its workgroup of a wide hidden layer (172 registers a lane from 257 columns
+// on) has a CU to itself, with nothing beside its error functions.  That shows once
+// each CU has more than four workgroups to run and these little else to do: inputs and
+// outputs of at most 3/4 of the hidden columns together where the columns leave waves
+// without a tile in the last round, of 3/8 where four rounds are full, and not where
+// three are.  Microseconds for 131072 rows, products and row kernel: 64-320-64 179 and
+// 216, 64-448-128 301 and 375, 64-512-64 318 and 343; but 64-384-64 215 and 222 (at
+// half the rows 110 and 101), 128-512-256 449 and 397, 192-320-256 313 and 270.
+static bool products_faster(kamx_mlp n, int R) {
+    const int round = 16 * kRowWaves, eighths = n->H % round ? 6 : (n->H > 3 * round ? 3 : 0);
+    return R > 4 * 32 * kRowLine && n->H > 2 * round && 8 * (n->fp + n->op) <= eighths * n->H;
+}
+
 // Activations of one forward pass: the normalised BF16 input, the two
 // BF16 hidden activations and, for training, the FP32 pre-activations and
 // normalised outputs (null when only the prediction is wanted).
@@ -1122,7 +1145,7 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
                                     long ldy, hipStream_t s) {
     const int R = pad64(batch), H = n->H, fp = n->fp, op = n->op;
     const Layout &L = n->L;
-    const bool rows = n->fused && !a.z1;
+    const bool rows = n->fused && !a.z1 && !products_faster(n, R);
     // the row kernel writes a workgroup's outputs while others still read their inputs, so
     // outputs over their inputs (the arrays share memory) have the inputs standardised
     // by a launch of their own
@@ -1143,28 +1166,32 @@ static kamx_status mlp_forward_rows(kamx_mlp n, const Acts &a, const float *x, l
         MLP_HIP(predict_rows(r, s));
         return KAMX_OK;
     }
-    EpiArgs e{};
-    e.bias = n->w + L.ob1;
-    e.f32 = a.z1;
-    e.b16 = a.h1;
-    e.ld = H;
-    MLP_HIP((gemm<kEpiHidden>(Operand{a.xh, fp, 1}, Operand{n->wb + L.bW1, fp, 1}, R, H, fp, e, s)));
-    e.bias = n->w + L.ob2;
-    e.f32 = a.z2;
-    e.b16 = a.h2;
-    MLP_HIP((gemm<kEpiHidden>(Operand{a.h1, H, 1}, Operand{n->wb + L.bW2, H, 1}, R, H, H, e, s)));
-    EpiArgs o{};
-    o.bias = n->w + L.ob3;
-    o.f32 = a.yn;
-    o.ld = op;
-    o.y = y;
-    o.ldy = ldy;
-    o.batch = batch;
-    o.n_out = n->n_out;
-    o.mu = n->mu_out;
-    o.sigma = n->sd_out;
-    MLP_HIP((gemm<kEpiOut>(Operand{a.h2, H, 1}, Operand{n->wb + L.bW3, H, 1}, R, op, H, o, s)));
-    return KAMX_OK;
+    auto layers = [&](auto blocked) {
+        constexpr bool kBlocked = decltype(blocked)::value;
+        EpiArgs e{};
+        e.bias = n->w + L.ob1;
+        e.f32 = a.z1;
+        e.b16 = a.h1;
+        e.ld = H;
+        MLP_HIP((gemm<kEpiHidden, kBlocked>(Operand{a.xh, fp, 1}, Operand{n->wb + L.bW1, fp, 1}, R, H, fp, e, s)));
+        e.bias = n->w + L.ob2;
+        e.f32 = a.z2;
+        e.b16 = a.h2;
+        MLP_HIP((gemm<kEpiHidden, kBlocked>(Operand{a.h1, H, 1}, Operand{n->wb + L.bW2, H, 1}, R, H, H, e, s)));
+        EpiArgs o{};
+        o.bias = n->w + L.ob3;
+        o.f32 = a.yn;
+        o.ld = op;
+        o.y = y;
+        o.ldy = ldy;
+        o.batch = batch;
+        o.n_out = n->n_out;
+        o.mu = n->mu_out;
+        o.sigma = n->sd_out;
+        MLP_HIP((gemm<kEpiOut, kBlocked>(Operand{a.h2, H, 1}, Operand{n->wb + L.bW3, H, 1}, R, op, H, o, s)));
+        return KAMX_OK;
+    };
+    return n->fused ? layers(std::true_type()) : layers(std::false_type());
 }
 
 static Acts own_acts(kamx_mlp n, bool keep) {

@@ -46,3 +46,22 @@ def test_learned_step_equals_external(hidden):
             m.close()
     net.close()
     cold.close()
+
+
+@pytest.mark.parametrize("n_in,hidden,n_out", [(20, 320, 60), (20, 448, 130), (64, 512, 64), (64, 384, 64), (128, 448, 65),
+                                               (20, 256, 20)])
+def test_large_batches(n_in, hidden, n_out):
+    """Above 32768 rows wide hidden layers between narrow ends predict through one product
+    per layer: the bits of the row kernel on a part of the rows, in place too."""
+    rng = np.random.default_rng(n_in + hidden)
+    n = 33000
+    net = device_net(random_net(rng, n_in, hidden, n_out), n)
+    x = torch.as_tensor(rng.normal(0, 2, (n, n_in)).astype(np.float32), device="cuda")
+    y = net.forward(x)
+    for lo, hi in ((0, 1000), (20000, 32768), (n - 300, n)):
+        assert torch.equal(y[lo:hi], net.forward(x[lo:hi].contiguous()))
+    buf = torch.zeros(n * max(n_in, n_out), dtype=torch.float32, device="cuda")
+    xv, yv = buf[:n * n_in].view(n, n_in), buf[:n * n_out].view(n, n_out)
+    xv.copy_(x)
+    assert torch.equal(net.forward(xv, out=yv), y)
+    net.close()
