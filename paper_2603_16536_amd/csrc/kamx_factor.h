@@ -218,7 +218,8 @@ __device__ __forceinline__ int factor_invert_tiles(float *A, float *Xs, int *fla
     if (T == 0) return 0;  // no rows: nothing has written the triangle
     if (wv == 0) factor_diag(0);
     __syncthreads();
-    for (int K = 0; K <= T; ++K) {
+    const int last = T > 1 ? T : 0;  // (one tile: P(0) puts its inverse in place)
+    for (int K = 0; K <= last; ++K) {
         if (uniform(*flag)) return 1;
         const int k0 = 16 * K, nI = T - K - 1;
         // ---- P(K)
