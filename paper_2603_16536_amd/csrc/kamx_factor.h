@@ -249,42 +249,46 @@ __device__ __forceinline__ int factor_invert_tiles(float *A, float *Xs, int *fla
             // X_ij = -sum_k M_ik X_kj of row i = K - 1: the diagonal tile X_jj
             // (lower triangular) first, then the full tiles below it, alternating
             // between two accumulators so consecutive products do not wait on
-            // each other
-            {
-                mfx4 xb[NX];
+            // each other; two tiles at a time, whose operands fit the registers (192
+            // rows on six waves have three, and all at once spilled 12 us' worth)
+            auto inverse_row = [&](auto first, auto count) {
+                constexpr int Q0 = first.value, NQ = count.value;
+                mfx4 xb[NQ];
 #pragma unroll
-                for (int q = 0; q < NX; ++q) xrow[q] = xb[q] = mfx4{0.f, 0.f, 0.f, 0.f};
+                for (int q = 0; q < NQ; ++q) xrow[Q0 + q] = xb[q] = mfx4{0.f, 0.f, 0.f, 0.f};
                 struct Terms {
-                    float m[4], x[NX][4];
+                    float m[4], x[NQ][4];
                 };
+                const int T0 = wv + Q0 * NWP;  // the first of this wave's tiles
                 auto read = [&](int Tk, Terms &h) {
                     load_tile_t(k0 - 16, 16 * Tk, h.m);
 #pragma unroll
                     for (int ch = 0; ch < 4; ++ch) {
                         const float *R = A + tri_row_offset(16 * Tk + 4 * ch + fk) + fr;
 #pragma unroll
-                        for (int q = 0; q < NX; ++q) h.x[q][ch] = R[16 * min(wv + q * NWP, Tk)];
+                        for (int q = 0; q < NQ; ++q) h.x[q][ch] = R[16 * min(T0 + q * NWP, Tk)];
                     }
                 };
                 auto multiply = [&](int Tk, Terms &h) {
 #pragma unroll
-                    for (int q = 0; q < NX; ++q) {
-                        const int Tj = wv + q * NWP;
+                    for (int q = 0; q < NQ; ++q) {
+                        const int Tj = T0 + q * NWP;
+                        mfx4 &x = xrow[Q0 + q];
                         if (Tj < Tk) {
 #pragma unroll
                             for (int ch = 0; ch < 4; ch += 2) {
-                                xrow[q] = mfma4(h.m[ch], h.x[q][ch], xrow[q]);
+                                x = mfma4(h.m[ch], h.x[q][ch], x);
                                 xb[q] = mfma4(h.m[ch + 1], h.x[q][ch + 1], xb[q]);
                             }
                         } else if (Tj == Tk) {
 #pragma unroll
                             for (int ch = 0; ch < 4; ++ch)
-                                xrow[q] = mfma4(h.m[ch], fr <= 4 * ch + fk ? h.x[q][ch] : 0.f, xrow[q]);
+                                x = mfma4(h.m[ch], fr <= 4 * ch + fk ? h.x[q][ch] : 0.f, x);
                         }
                     }
                 };
                 Terms ha, hb;
-                int Tk = wv;
+                int Tk = T0;
                 if (Tk < K - 1) read(Tk, ha);
                 for (; Tk + 1 < K - 1; Tk += 2) {
                     read(Tk + 1, hb);
@@ -294,8 +298,11 @@ __device__ __forceinline__ int factor_invert_tiles(float *A, float *Xs, int *fla
                 }
                 if (Tk < K - 1) multiply(Tk, ha);
 #pragma unroll
-                for (int q = 0; q < NX; ++q) xrow[q] += xb[q];
-            }
+                for (int q = 0; q < NQ; ++q) xrow[Q0 + q] += xb[q];
+            };
+            static_assert(NX <= 4, "tiles of an inverse row per wave");
+            inverse_row(Const<0>{}, Const<(NX < 2 ? NX : 2)>{});
+            if constexpr (NX > 2) inverse_row(Const<2>{}, Const<NX - 2>{});
         }
         __syncthreads();
         // ---- T(K)
