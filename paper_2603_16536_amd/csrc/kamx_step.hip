@@ -544,8 +544,10 @@ constexpr int kSolveConverged = 1 << 8;  // beside the KAMX_WORLD bits in solve_
 // residual, so the fixed point solves the linear system to the accuracy of the
 // residual, not to cond(D~) times FP32 epsilon.
 //
-// Out of line, so that the registers of its loop are its own.  Hands over, in
-// s_int: [4] the next iteration, [5] status bits and kSolveConverged, [6..8] r_p,
+// Inlined into the kernel, whose other functions hold nothing in registers while it
+// runs and which has no caller's registers to keep: as a function of its own it
+// stored and loaded 85 to 101 registers a lane, which at a workgroup on every CU went
+// past the L2 and took 6 to 7 us of a step.  Hands over, in s_int: [4] the next iteration, [5] status bits and kSolveConverged, [6..8] r_p,
 // r_d, r_c; the iterates x, y, z (and y, z as the extrapolated ones) and D~ x in
 // their fields.
 //
@@ -556,20 +558,14 @@ constexpr int kSolveConverged = 1 << 8;  // beside the KAMX_WORLD bits in solve_
 // iterates) and a phase is left with one round of LDS reads of what other threads
 // wrote, all issued before the first is used.  On the biped (224 rows, one world
 // of eight waves per compute unit) an iteration takes 3.0 us against 5.2 us with
-// every operand read from LDS where it is used.
+// every operand read from LDS where it is used.  Sums of two products name the one that
+// is fused: the compiler takes either, by the function around them.
 template <int MC, int NT>
-__device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int m, int nb, int nc, int row_c0,
-                                                    int nlim, int it) {
-    const int tid = threadIdx.x;
-    KernelArgs &a = *uniform_args(args);
+__device__ __forceinline__ int solve_pass(KernelArgs &a, int w, int m, int nb, int nc, int row_c0, int nlim, int it) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // addresses formed here, not held through the kernel's loops
     SolverArgs &P = a.p;
-    w = uniform(w);
-    m = uniform(m);
-    nb = uniform(nb);
-    nc = uniform(nc);
-    row_c0 = uniform(row_c0);
-    it = uniform(it);
-    const int n_uni = uniform(nlim) + 3 * nc;  // limit and contact rows: what the adaptive penalty acts on
+    const int n_uni = nlim + 3 * nc;  // limit and contact rows: what the adaptive penalty acts on
     const Lds L = lds_views<MC>();
     const float *A = L.A;
     float *vp = L.vec(VP), *vrho = L.vec(VRHO), *vvt = L.vec(VVT);
@@ -750,7 +746,7 @@ __device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int
     // against the current x
     auto put_rhs = [&]() {
         if (owner_o) {
-            const float s_own = kind_o == kRowNormal ? mu_o * hw_sqrt(ozh[1] * ozh[1] + ozh[2] * ozh[2]) : 0.f;
+            const float s_own = kind_o == kRowNormal ? mu_o * hw_sqrt(__builtin_fmaf(ozh[1], ozh[1], ozh[2] * ozh[2])) : 0.f;
             _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
                 float rhs = -ovt[e] - (e == 0 ? s_own : 0.f) + eta * ox[e] + orho * oyh[e] + ozh[e];
                 vrhs[io + e] = rhs - (odx[e] + (eta + orho) * ox[e]);
@@ -948,7 +944,7 @@ __device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int
             if (kind_o == kRowNormal) {
                 // the cone's three cases as selections (proj_cone's values)
                 const float w0 = ox[0] - ozh[0] * ori, w1 = ox[1] - ozh[1] * ori, w2 = ox[2] - ozh[2] * ori;
-                const float tn = hw_sqrt(w1 * w1 + w2 * w2);
+                const float tn = hw_sqrt(__builtin_fmaf(w1, w1, w2 * w2));
                 const float mt = mu_o * tn, ln = add_rounded(mt, w0) * cone_o;
                 const float sc = tn > 0.f ? mu_o * ln * hw_rcp(tn) : 0.f;
                 const bool in = tn <= mu_o * w0, below = mt <= -w0;
@@ -964,15 +960,15 @@ __device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int
                 zb[e] = ozh[e] - orho * (ox[e] - yb[e]);
                 lrp = fmaxf(lrp, fabsf(ox[e] - yb[e]));
                 float dy = yb[e] - oyh[e], dz = zb[e] - ozh[e];
-                lcc += orho * dy * dy + dz * dz * ori;
+                lcc += __builtin_fmaf(orho * dy, dy, dz * dz * ori);
             }
-            float g = kind_o == kRowNormal ? mu_o * hw_sqrt(vv[1] * vv[1] + vv[2] * vv[2]) : 0.f;
+            float g = kind_o == kRowNormal ? mu_o * hw_sqrt(__builtin_fmaf(vv[1], vv[1], vv[2] * vv[2])) : 0.f;
             _Pragma("unroll") for (int e = 0; e < 3; ++e) if (e < blk_o) {
                 float d = vv[e] + (e == 0 ? g : 0.f) - zb[e];
                 lrd = fmaxf(lrd, fabsf(d));
                 if (d != d) lrd = fabsf(d);
             }
-            if (kind_o == kRowNormal) lrc = fabsf(yb[0] * (vv[0] + g) + yb[1] * vv[1] + yb[2] * vv[2]);
+            if (kind_o == kRowNormal) lrc = fabsf(__builtin_fmaf(yb[2], vv[2], __builtin_fmaf(yb[0], vv[0] + g, yb[1] * vv[1])));
             else if (kind_o == kRowLimit) lrc = fabsf(yb[0] * vv[0]);
             if (lrp != lrp || lcc != lcc) lrp = NAN;
         }
@@ -1075,11 +1071,21 @@ __device__ __attribute__((noinline)) int solve_pass(KernelArgs *args, int w, int
     return adapt_pending;
 }
 
-// One step of world w (every phase of the step; the workgroup owns the
-// world).  step is the step index that keys the actuation noise; k the
-// position of the step inside the launch.
+// One step of world w in three parts (the workgroup owns the world): its rows and their
+// factor, the solve, and the outputs.  step is the step index that keys the
+// actuation noise; k the position of the step inside the launch.
+
+// Rows of a world in the layout its contacts give it.
+struct RowCounts {
+    int nc, c0, m;  // contacts, first contact row, rows
+    __device__ inline RowCounts(const WorldInfo &W, const Lds &L)
+        : nc(uniform(L.s_int[1])), c0(5 * W.nj + W.nlim + W.ndrv), m(c0 + 3 * nc) {}
+};
+
+// From the bodies to the factor inverse.  Returns whether the factorization failed, or -1
+// where the launch ends with the step's features.
 template <int MC, int NT>
-__device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
+__device__ __attribute__((noinline)) int step_begin(KernelArgs *args, int k) {
     const int tid = threadIdx.x;
     KernelArgs &a = *uniform_args(args);
     k = uniform(k);
@@ -1212,7 +1218,7 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
     if (a.stage == 1) {
         float *f = a.features + (long)w * a.n_feat;
         for (int t = tid; t < a.n_feat; t += NT) f[t] = feature(t);
-        return;
+        return -1;
     }
 
     // ---- learned warm start: the network predicts this world's impulses by
@@ -1386,11 +1392,10 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
         }
     }
     __syncthreads();
-    const int nc = uniform(s_int[1]);
+    const RowCounts rows(W, L);
+    const int nc = rows.nc, row_c0 = rows.c0, m = rows.m;
     const int row_lim0 = 5 * nj;
     const int row_drv0 = 5 * nj + W.nlim;
-    const int row_c0 = row_drv0 + W.ndrv;
-    const int m = row_c0 + 3 * nc;
 
     // ---- constraint rows
     for (int j = tid; j < nj; j += NT) {
@@ -1713,56 +1718,81 @@ __device__ __attribute__((noinline)) void step_world(KernelArgs *args, int k) {
     const int factor_fail = uniform(factor_invert<MC, NT>(m));
     if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 4] = wall_clock64();
     if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 5] = wall_clock64();
-    // ---- PADMM (Alg. 1 steps 3-10).  The x-update of step 5 is computed as
-    //      x + X^T X (rhs - (D~ + eta + rho) x): one refinement step from the
-    //      previous iterate with the FP32 factor inverse and an FP64
-    //      matrix-free residual, so the fixed point solves the linear system
-    //      to the accuracy of the residual, not to cond(D~) times FP32 epsilon.
-    const float eta = P.eta;
-    const float mu_i = i < m ? L.rf(RMU, i) : 0.f;
-    int it = 0, status = 0;
-    float rp = 0.f, rd = 0.f, rc = 0.f, rncp = 0.f;
-    const int N = P.fixed_iters > 0 ? P.fixed_iters : P.max_iters;
     if (i < m) vrinv[i] = 1.f / vrho[i];  // rho is fixed for the solve: divide once
+    if (factor_fail) {
+        if (i < m) vyp[i] = 0.f;
+    } else if (wmode == KAMX_WARM_COLD && i < m) {
+        vx[i] = vyh[i] = vzh[i] = vyp[i] = vzp[i] = vdx[i] = 0.f;
+    }
+    __syncthreads();
+    return factor_fail;
+}
+
+// The solve (Alg. 1 steps 3-10), in passes: a pass ends when the solve exits or when the
+// adaptive penalty changes rho, whose refactorization then runs outside the iteration
+// loop.  Returns KAMX_WORLD_FACTOR_FAIL if that fails, else 0.
+template <int MC, int NT>
+__device__ __forceinline__ int step_solve(KernelArgs &a) {
+    const int tid = threadIdx.x;
+    const int w = uniform(a.bucket_worlds[blockIdx.x]);
+    const WorldInfo W = uniform_world(a.worlds + w);
+    const Lds L = lds_views<MC>();
+    const RowCounts rows(W, L);
+    int it = 1;
+    for (;;) {
+        const int adapt = solve_pass<MC, NT>(a, w, rows.m, W.nb, rows.nc, rows.c0, W.nlim, it);
+        if (!adapt) return 0;
+        it = uniform(L.s_int[4]);
+        // the limit and contact rows' penalty changes by the factor; D~ +
+        // diag(eta + rho) is rebuilt, refactored and inverted, and the
+        // acceleration restarts at the current (y, z), which the owners have
+        // written as the extrapolated iterates
+        const float f = adapt == 1 ? 1.f / a.p.adapt_factor : a.p.adapt_factor;
+        float *vrho = L.vec(VRHO), *vrinv = L.vec(VCOL);
+        __syncthreads();
+        for (int r = tid; r < rows.m; r += NT)
+            if (L.ri(RKIND, r) != kRowBilateral) {
+                vrho[r] *= f;
+                vrinv[r] = 1.f / vrho[r];
+            }
+        __syncthreads();
+        reassemble<MC, NT>(rows.m, W.nb, a.p.eta);
+        if (uniform(factor_invert<MC, NT>(rows.m))) return KAMX_WORLD_FACTOR_FAIL;
+    }
+}
+
+// Residual of the returned iterate, outputs, and the velocities and poses it leads to.
+// factor_fail: the step's own factorization failed (no solve); status: of the solve.
+template <int MC, int NT>
+__device__ __attribute__((noinline)) void step_end(KernelArgs *args, int k, int factor_fail, int status) {
+    const int tid = threadIdx.x, i = tid;
+    KernelArgs &a = *uniform_args(args);
+    k = uniform(k);
+    factor_fail = uniform(factor_fail);
+    status = uniform(status);
+    const int w = uniform(a.bucket_worlds[blockIdx.x]);
+    const WorldInfo W = uniform_world(a.worlds + w);
+    SolverArgs &P = a.p;
+    const Lds L = lds_views<MC>();
+    const int *s_int = L.s_int;
+    const int nb = W.nb;
+    const RowCounts rows(W, L);
+    const int nc = rows.nc, m = rows.m;
+    const int *cint = reinterpret_cast<const int *>(L.c);
+    float *vp = L.vec(VP), *vvt = L.vec(VVT);
+    float *vx = L.vec(VX), *vyp = L.vec(VYP), *vzp = L.vec(VZP), *vaux = L.vec(VAUX);
+    const int kind_i = i < m ? L.ri(RKIND, i) : -1;
+    const bool owner = i < m && kind_i != kRowTangent;
+    const int blk = kind_i == kRowNormal ? 3 : 1;
+    const float mu_i = i < m ? L.rf(RMU, i) : 0.f;
+    const int N = P.fixed_iters > 0 ? P.fixed_iters : P.max_iters;
+    int it = 0;
+    float rp = 0.f, rd = 0.f, rc = 0.f, rncp = 0.f;
     if (factor_fail) {
         status = KAMX_WORLD_FACTOR_FAIL;
         rp = rd = rc = rncp = NAN;
-        if (i < m) vyp[i] = 0.f;
     } else {
-        if (wmode == KAMX_WARM_COLD && i < m) {
-            vx[i] = vyh[i] = vzh[i] = vyp[i] = vzp[i] = vdx[i] = 0.f;
-        }
-        // the solve runs in passes: a pass ends when the solve exits or when
-        // the adaptive penalty changes rho, whose refactorization then runs
-        // outside the iteration loop
-        int it_next = 1;
-        __syncthreads();
-        for (;;) {
-            const int adapt_pending =
-                solve_pass<MC, NT>(args, w, m, nb, nc, row_c0, W.nlim, it_next);
-            it_next = uniform(s_int[4]);
-            if (!adapt_pending) break;
-            {
-                // the limit and contact rows' penalty changes by the factor;
-                // D~ + diag(eta + rho) is rebuilt, refactored and inverted, and
-                // the acceleration restarts at the current (y, z), which the
-                // owners have written as the extrapolated iterates
-                const float f = adapt_pending == 1 ? 1.f / P.adapt_factor : P.adapt_factor;
-                __syncthreads();
-                for (int r = tid; r < m; r += NT)
-                    if (L.ri(RKIND, r) != kRowBilateral) {
-                        vrho[r] *= f;
-                        vrinv[r] = 1.f / vrho[r];
-                    }
-                __syncthreads();
-                reassemble<MC, NT>(m, nb, eta);
-                if (uniform(factor_invert<MC, NT>(m))) {
-                    status = KAMX_WORLD_FACTOR_FAIL;
-                    break;
-                }
-            }
-        }
-        it = it_next;
+        it = uniform(s_int[4]);
         status |= uniform(s_int[5]) & ~kSolveConverged;
         const bool converged = uniform(s_int[5]) & kSolveConverged;
         rp = __int_as_float(uniform(s_int[6]));
@@ -1888,7 +1918,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void st
     KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
 #pragma clang loop unroll(disable)
     for (int k = 0; k < a.nsteps; ++k) {
-        step_world<MC, NT>(args, k);
+        const int failed = uniform(step_begin<MC, NT>(args, k));
+        if (failed >= 0) step_end<MC, NT>(args, k, failed, failed ? 0 : step_solve<MC, NT>(*args));
         __syncthreads();
     }
 }
