@@ -179,6 +179,21 @@ __device__ inline KernelArgs *uniform_args(KernelArgs *a) {
     return (KernelArgs *)(((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v));
 }
 
+// What the iteration would do in a world without rows, whose residuals are zero: the
+// iterations until it exits (0 < eps: the first), and their restart log (the restart
+// sum falls to zero at the first iteration and not below afterwards).  Every thread
+// of the workgroup calls.
+template <int NT>
+__device__ inline int iterations_without_rows(KernelArgs &a, int w, bool &converged) {
+    SolverArgs &P = a.p;
+    converged = P.fixed_iters <= 0 && 0.f < P.eps;
+    const int it = converged ? 1 : (P.fixed_iters > 0 ? P.fixed_iters : P.max_iters);
+    if (a.rlog && P.log_restarts)
+        for (int j = threadIdx.x; j < min(it, P.max_iters); j += NT)
+            a.rlog[(size_t)w * P.max_iters + j] = P.accel && j > 0 ? 1 : 0;
+    return it;
+}
+
 // A world's record as scalars.
 __device__ inline WorldInfo uniform_world(const WorldInfo *w) {
     WorldInfo W;

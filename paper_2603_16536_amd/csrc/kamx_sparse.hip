@@ -1028,7 +1028,20 @@ __device__ __attribute__((noinline)) void sparse_step_world(KernelArgs *args, in
     L.rf(SRREG, tid) = R.preg;
     L.ri(SRKIND, tid) = R.kind;
     __syncthreads();
-    sp_solve<NT>(args, w, nb, rc0p, W.nlim + 3 * nc, wmode != KAMX_WARM_COLD);
+    if (m > 0) {
+        sp_solve<NT>(args, w, nb, rc0p, W.nlim + 3 * nc, wmode != KAMX_WARM_COLD);
+    } else {
+        bool converged;
+        const int n = iterations_without_rows<NT>(a, w, converged);
+        if (tid == 0) {
+            s_int[4] = n;
+            s_int[5] = converged || P.fixed_iters > 0 ? 0 : KAMX_WORLD_MAXITER;
+            s_int[6] = s_int[7] = s_int[8] = s_int[9] = 0;  // r_p, r_d, r_c, r_ncp
+        }
+        L.rf(SRBIAS, tid) = L.rf(SRMU, tid) = L.rf(SRREG, tid) = 0.f;  // x, y, z
+        for (int t = tid; t < 6 * nb; t += NT) L.g[t] = 0.0;
+        __syncthreads();
+    }
     const float x = L.rf(SRBIAS, tid), yp = L.rf(SRMU, tid), zp = L.rf(SRREG, tid);
     const int it = s_int[4], status = s_int[5];
     const float rp = __int_as_float(s_int[6]), rd = __int_as_float(s_int[7]), rc = __int_as_float(s_int[8]),

@@ -1082,8 +1082,10 @@ struct RowCounts {
         : nc(uniform(L.s_int[1])), c0(5 * W.nj + W.nlim + W.ndrv), m(c0 + 3 * nc) {}
 };
 
-// From the bodies to the factor inverse.  Returns whether the factorization failed, or -1
-// where the launch ends with the step's features.
+// What is left of a step once its rows are built.
+enum StepLeft { kStepFeatures = -1 /* nothing: the launch wanted the features */, kStepSolve, kStepFailed, kStepNoRows };
+
+// From the bodies to the factor inverse.
 template <int MC, int NT>
 __device__ __attribute__((noinline)) int step_begin(KernelArgs *args, int k) {
     const int tid = threadIdx.x;
@@ -1218,7 +1220,7 @@ __device__ __attribute__((noinline)) int step_begin(KernelArgs *args, int k) {
     if (a.stage == 1) {
         float *f = a.features + (long)w * a.n_feat;
         for (int t = tid; t < a.n_feat; t += NT) f[t] = feature(t);
-        return -1;
+        return kStepFeatures;
     }
 
     // ---- learned warm start: the network predicts this world's impulses by
@@ -1724,8 +1726,17 @@ __device__ __attribute__((noinline)) int step_begin(KernelArgs *args, int k) {
     } else if (wmode == KAMX_WARM_COLD && i < m) {
         vx[i] = vyh[i] = vzh[i] = vyp[i] = vzp[i] = vdx[i] = 0.f;
     }
+    if (m == 0) {
+        bool converged;
+        const int it = iterations_without_rows<NT>(a, w, converged);
+        if (tid == 0) {
+            s_int[4] = it;
+            s_int[5] = converged ? kSolveConverged : 0;
+            s_int[6] = s_int[7] = s_int[8] = 0;  // r_p, r_d, r_c
+        }
+    }
     __syncthreads();
-    return factor_fail;
+    return m == 0 ? kStepNoRows : (factor_fail ? kStepFailed : kStepSolve);
 }
 
 // The solve (Alg. 1 steps 3-10), in passes: a pass ends when the solve exits or when the
@@ -1762,13 +1773,13 @@ __device__ __forceinline__ int step_solve(KernelArgs &a) {
 }
 
 // Residual of the returned iterate, outputs, and the velocities and poses it leads to.
-// factor_fail: the step's own factorization failed (no solve); status: of the solve.
+// left: what step_begin returned; status: of the solve.
 template <int MC, int NT>
-__device__ __attribute__((noinline)) void step_end(KernelArgs *args, int k, int factor_fail, int status) {
+__device__ __attribute__((noinline)) void step_end(KernelArgs *args, int k, int left, int status) {
     const int tid = threadIdx.x, i = tid;
     KernelArgs &a = *uniform_args(args);
     k = uniform(k);
-    factor_fail = uniform(factor_fail);
+    const bool factor_fail = uniform(left) == kStepFailed;
     status = uniform(status);
     const int w = uniform(a.bucket_worlds[blockIdx.x]);
     const WorldInfo W = uniform_world(a.worlds + w);
@@ -1918,8 +1929,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void st
     KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
 #pragma clang loop unroll(disable)
     for (int k = 0; k < a.nsteps; ++k) {
-        const int failed = uniform(step_begin<MC, NT>(args, k));
-        if (failed >= 0) step_end<MC, NT>(args, k, failed, failed ? 0 : step_solve<MC, NT>(*args));
+        const int left = uniform(step_begin<MC, NT>(args, k));
+        if (left >= kStepSolve) step_end<MC, NT>(args, k, left, left > kStepSolve ? 0 : step_solve<MC, NT>(*args));
         __syncthreads();
     }
 }

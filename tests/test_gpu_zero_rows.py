@@ -80,3 +80,29 @@ def test_beside_and_after_contacts(points):
     m.step(1)
     check(m, ref, np.arange(WORLDS))
     m.close()
+
+
+@pytest.mark.parametrize("solver", ["dense", "sparse"])
+@pytest.mark.parametrize("over,iters,status,log", [
+    (dict(), 1, 0, [0]),
+    (dict(eps=0.0, max_iters=7), 7, 1, [0, 1, 1, 1, 1, 1, 1]),
+    (dict(fixed_iters=4, max_iters=6), 4, 0, [0, 1, 1, 1]),
+    (dict(fixed_iters=4, max_iters=3, accel=0), 4, 0, [0, 0, 0]),
+    (dict(fixed_iters=3, max_iters=3, warmstart=1), 3, 0, [0, 1, 1])])
+def test_what_the_iteration_would_report(solver, over, iters, status, log):
+    """Iterations, status and restart log of worlds without rows are those of the loop on
+    zero residuals: out at the first iteration, unless eps or a fixed count keep it
+    going; every later one restarts the acceleration."""
+    scene = without_contacts(boxes(5, 900))
+    p = dict(P, log_restarts=1, linear_solver=kamx.SOLVER_SPARSE if solver == "sparse" else kamx.SOLVER_DENSE)
+    p.update(over)
+    m = kamx.Model(scene, params=p, max_contacts=5)
+    m.upload_contacts(scene)
+    m.step(2)
+    st = {k: v.cpu().numpy() for k, v in m.stats().items()}
+    assert np.all(st["rows"] == 0) and np.all(st["resid"] == 0)
+    assert np.all(st["iters"] == iters) and np.all(st["status"] == status)
+    got = m.restart_log().cpu().numpy()[:, :len(log)]
+    assert np.array_equal(got, np.tile(np.array(log, np.uint8), (WORLDS, 1)))
+    assert np.all(m.impulses().cpu().numpy() == 0)
+    m.close()
