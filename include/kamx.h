@@ -454,7 +454,8 @@ kamx_status kamx_reset_count(kamx_model m, int64_t *count, kamx_stream stream);
 
 /* Diagnostic: wall-clock stamps (device ticks) of the last step of every
  * world into clk_dev [n_worlds*16]: entries 0-7 at the phase boundaries
- * (start, Delassus, warm start, factor, inverse, iterations, outputs, end),
+ * (start, Delassus, warm start, factor, inverse, iterations, outputs, end; the
+ * inverse is formed with the factor, so that entry 5 equals entry 4),
  * entries 8-13 the ticks spent in the iteration sub-phases (right-hand side,
  * forward mat-vec, transposed mat-vec, body gather, projections and
  * residuals, updates), entry 14 the index of the compute unit that ran the

@@ -14,7 +14,11 @@
 // LDS in FP32 and factored and inverted on the matrix cores by the step kernel's
 // tile factorization, so that the solve is two triangular products; F and the
 // poses stay FP64, so the iteration converges to FP64-level constraint residuals
-// with FP32 linear solves.  Runs once per reset, not per step.
+// with FP32 linear solves.  Pivots are the hardware's reciprocals and reciprocal square
+// roots (1 ulp), and a product with the explicit inverse rounds otherwise than a
+// substitution: a step differs from one with exact pivots in its last bits, the
+// poses it converges to by less than 3e-8.  A pivot that is not positive and finite
+// fails the world.  Runs once per reset, not per step.
 //
 // An iteration is bound by the factorization's serial diagonal tiles and, like the
 // step, by one world per compute unit (the triangle fills its LDS).  1024 bipeds

@@ -322,7 +322,9 @@ __global__ void set_norm_kernel(const float *mu_in, const float *sd_in, int n_in
 // (eight ahead, or every line touched at the start, gained nothing).  Every sum over
 // K runs in the order of gemm_kernel, so outputs have its bits.  15.5 us for the
 // batch of 1000 (3 standardising, 4 in the first layer's 360 KB of weights, 2 in each
-// hidden layer's error functions, 3 of launch); a training batch of 4096 takes 31 us.
+// hidden layer's error functions, 3 of launch) on weights and inputs that are in the caches
+// (42 us on inputs not seen before, 67 us in four launches); a training batch of 4096
+// takes 31 us.
 
 constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
 constexpr int kRowTiles = 4;  // hidden column tiles a wave keeps, at most
@@ -355,7 +357,12 @@ inline size_t row_lds_bytes(int fp, int H, int op, int mb, bool train) {
 }
 
 // Networks whose rows fit 64 KB of LDS and whose hidden columns fit the registers;
-// wider ones go through one product per layer.
+// wider ones go through one product per layer.  Training keeps the derivatives of both
+// hidden layers: 385 to 512 columns spill 115 registers a lane, 257 to 384 nine, and
+// are still the faster path at every batch from 1 to 65536.  Microseconds of a
+// training step, row kernel and one product per layer: 667-384-224 50 and 123 for 64
+// rows, 74 and 235 for 4096, 1101 and 2214 for 65536; 667-512-224 77 and 130, 107 and
+// 248, 1691 and 2559; 64-512-64 53 and 111, 76 and 193, 1109 and 1588.
 inline bool rows_kernel_takes(int fp, int H, int op) {
     return H <= 16 * kRowTiles * kRowWaves && row_lds_bytes(fp, H, op, 1, true) <= kPlainLds;
 }
@@ -1053,10 +1060,11 @@ static hipError_t launch_rows_mb(const RowArgs &r, hipStream_t s) {
 }
 
 // A prediction takes 16 rows a workgroup while that is not more than one workgroup per
-// CU, then 32, which halves the weights' traffic: on the biped's network 17.8 us
-// against 20.5 for 4096 rows, but 29.4 against 23.3 for 8192 (before the biases were
-// loaded early).  (Training keeps two
-// layers' derivatives in registers and takes 16.)
+// CU, then 32, which halves the weights' traffic.  Microseconds of 16 and 32 rows a
+// workgroup: 667-256-224 15.4 and 16.8 for 4096 rows, 23.3 and 16.8 for 4160, 25.8 and
+// 19.3 for 8192; 1300-256-100, whose 32 rows take 107 KB of LDS, 23.9 and 25.8, 36.4 and
+// 26.0, 38.0 and 27.6; 667-512-224 32.7 and 36.3, 63.2 and 37.3, 66.8 and 39.0.  (Training
+// keeps two layers' derivatives in registers and takes 16.)
 static hipError_t predict_rows(const RowArgs &r, hipStream_t s) {
     return r.R > 16 * kRowLine ? launch_rows_mb<2, false>(r, s) : launch_rows_mb<1, false>(r, s);
 }

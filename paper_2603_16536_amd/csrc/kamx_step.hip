@@ -163,15 +163,6 @@ __device__ inline void joint_rows(const Lds &L, int type, const JointGeo &g, int
 // index order), results uniform across the workgroup
 // ---------------------------------------------------------------------------
 
-
-// ---------------------------------------------------------------------------
-// matrix-free preconditioned Delassus product out = P J M^-1 J^T P x (Eq. 4),
-// accumulated in FP64 over the two 6-blocks of every row: bodies gather
-// their incident rows (fixed row order), rows then read their two bodies.
-// Costs O(rows) instead of O(rows^2); used for the refinement residual of
-// every x-update and for the dual residual.
-// ---------------------------------------------------------------------------
-
 template <int NT>
 __device__ inline void reduce4(float &m0, float &m1, float &m2, float &s3, float *red) {
     // rows of 16 lanes by DPP, then the wave's four rows through readlane,
@@ -247,6 +238,14 @@ constexpr int default_bucket_threads(int mc) {
         if (v.mc == mc) return v.nt[0];
     return 0;
 }
+
+// ---------------------------------------------------------------------------
+// matrix-free preconditioned Delassus product out = P J M^-1 J^T P x (Eq. 4),
+// accumulated in FP64 over the two 6-blocks of every row: bodies gather
+// their incident rows (fixed row order), rows then read their two bodies.
+// Costs O(rows) instead of O(rows^2); used for the refinement residual of
+// every x-update and for the dual residual.
+// ---------------------------------------------------------------------------
 
 // Body gather of the matrix-free product: g_b = sum over the rows incident
 // to body b of J_{r,b}^T p_r x_r, one thread per (body, component), FP64,
@@ -1718,8 +1717,8 @@ __device__ __attribute__((noinline)) int step_begin(KernelArgs *args, int k) {
 
     if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 3] = wall_clock64();
     const int factor_fail = uniform(factor_invert<MC, NT>(m));
-    if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 4] = wall_clock64();
-    if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 5] = wall_clock64();
+    // (the inverse comes with the factor: both stamps)
+    if (a.phase_clk && tid == 0) a.phase_clk[16 * w + 4] = a.phase_clk[16 * w + 5] = wall_clock64();
     if (i < m) vrinv[i] = 1.f / vrho[i];  // rho is fixed for the solve: divide once
     if (factor_fail) {
         if (i < m) vyp[i] = 0.f;
@@ -1921,9 +1920,9 @@ __device__ __attribute__((noinline)) void step_end(KernelArgs *args, int k, int 
 // workgroup keeping its world for all of them: worlds are independent, so a
 // slow solve delays only its own world and the hardware's dispatch balances
 // whole chains of steps rather than single steps.
-// At most 256 VGPRs (two waves per SIMD): the per-step function needs 248,
-// and a workgroup smaller than 512 threads then leaves room on its compute
-// unit for another world's workgroup.
+// At most 256 VGPRs (two waves per SIMD), which the solve and the factorization use to
+// the last ten; a workgroup smaller than 512 threads then leaves room on its
+// compute unit for another world's workgroup.
 template <int MC, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel(StepArgs a) {
     KernelArgs *args = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
