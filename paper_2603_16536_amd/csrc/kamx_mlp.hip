@@ -1129,14 +1129,15 @@ static hipError_t train_fused(kamx_mlp n, const float *x, const float *target, i
 // fits it: its workgroup of a wide hidden layer (172 registers a lane from 257 columns
 // on) has a CU to itself, with nothing beside its error functions.  That shows once
 // each CU has more than four workgroups to run and these little else to do: inputs and
-// outputs of at most 3/4 of the hidden columns together where the columns leave waves
-// without a tile in the last round, of 3/8 where four rounds are full, and not where
-// three are.  Microseconds for 131072 rows, products and row kernel: 64-320-64 179 and
+// outputs of at most 3/4 of the hidden columns together where the columns leave some of
+// the waves a tile short, of 3/8 where every wave has four, and not where every wave
+// has three.  Microseconds for 131072 rows, products and row kernel: 64-320-64 179 and
 // 216, 64-448-128 301 and 375, 64-512-64 318 and 343; but 64-384-64 215 and 222 (at
 // half the rows 110 and 101), 128-512-256 449 and 397, 192-320-256 313 and 270.
 static bool products_faster(kamx_mlp n, int R) {
-    const int round = 16 * kRowWaves, eighths = n->H % round ? 6 : (n->H > 3 * round ? 3 : 0);
-    return R > 4 * 32 * kRowLine && n->H > 2 * round && 8 * (n->fp + n->op) <= eighths * n->H;
+    const int each = 16 * kRowWaves;  // hidden columns at a tile to a wave
+    const int eighths = n->H % each ? 6 : (n->H > 3 * each ? 3 : 0);
+    return R > 4 * 32 * kRowLine && n->H > 2 * each && 8 * (n->fp + n->op) <= eighths * n->H;
 }
 
 // Activations of one forward pass: the normalised BF16 input, the two
